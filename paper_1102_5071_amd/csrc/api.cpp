@@ -16,6 +16,7 @@
 
 #include "cfet_internal.h"
 #include "host_common.h"
+#include "parity.h"
 
 using cfet::DevCSR;
 using cfet::DevStats;
@@ -34,6 +35,7 @@ struct cfet_ctx {
   int nb_tile = 0;          // and their grid
   bool tile_real = false;   // every value stored in the split layout is real
   bool use_sell = false;
+  cfet::DevParity parity;   // site-operator form (parity.ok: the products run on it)
   int64_t sell_bytes = 0;   // stored SELL data one application reads
   // row order of the CSR paths (null: the caller's): row i of the stored
   // operator is the caller's row perm[i], caller row j is row iperm[j];
@@ -94,6 +96,8 @@ thread_local std::string g_err;
 // automatic path choice by dimension
 constexpr int64_t kAutoSingleMaxN = 4096;
 constexpr int64_t kAutoCoopMaxN = int64_t(1) << 22;
+// smallest dimension of the sweeps on the site-operator form
+constexpr int64_t kParityMinN = int64_t(1) << 16;
 // Grid of the cooperative kernel: one block per CU, but at least ~128 rows per
 // block; each block owns ceil(n / blocks) consecutive rows.
 int64_t coop_grid_blocks(int64_t n, int cus) {
@@ -210,6 +214,9 @@ void free_ctx(cfet_ctx* c) {
   if (c->sell.cval) (void)hipFree(c->sell.cval);
   if (c->hi.ccolt) (void)hipFree(c->hi.ccolt);
   if (c->hi.cval) (void)hipFree(c->hi.cval);
+  if (c->parity.diag) (void)hipFree(c->parity.diag);
+  if (c->parity.e) (void)hipFree(c->parity.e);
+  if (c->parity.part) (void)hipFree(c->parity.part);
   if (c->basis) (void)hipFree(c->basis);
   if (c->partA) (void)hipFree(c->partA);
   if (c->partB) (void)hipFree(c->partB);
@@ -245,8 +252,12 @@ int ensure_workspace(cfet_ctx* c, int m) {
     c->basis = nullptr;
     c->m_alloc = 0;
   }
-  const size_t bytes = size_t(m - 1) * size_t(c->n) * sizeof(double2);
-  if (bytes > 0) {
+  // The sweeps read several basis vectors at the same offsets at once: 256
+  // bytes between vectors of a power-of-two length keep them off the same
+  // memory channels (the chain of 24: 484 -> 464 us per iteration).
+  const size_t stride = size_t(c->n) + (c->parity.ok ? 16 : 0);
+  const size_t bytes = (size_t(m - 1) * stride + (c->parity.ok ? 16 : 0)) * sizeof(double2);
+  if (m > 1) {
     e = hipMalloc(&c->basis, bytes);
     if (e != hipSuccess) {
       (void)hipGetLastError();
@@ -256,7 +267,8 @@ int ensure_workspace(cfet_ctx* c, int m) {
     }
   }
   c->h_W.assign(cfet::kMaxM, nullptr);
-  for (int j = 1; j < m; ++j) c->h_W[j] = c->basis + size_t(j - 1) * size_t(c->n);
+  for (int j = 1; j < m; ++j)
+    c->h_W[j] = c->basis + (c->parity.ok ? 16 : 0) + size_t(j - 1) * stride;
   c->m_alloc = m;
   return CFET_OK;
 }
@@ -326,7 +338,9 @@ bool single_fits(const cfet_ctx* c) { return c->preset_single >= 0; }
 
 bool coop_fits(const cfet_ctx* c) { return c->preset_coop >= 0 && c->coop_blocks > 0; }
 
-int choose_path(const cfet_ctx* c) {
+// The path of the persistent kernels' callers (cfet_gradient): without the
+// sweeps on the site-operator form, which only propagation uses.
+int choose_path_csr(const cfet_ctx* c) {
   if (c->flags & CFET_FORCE_MULTIKERNEL) return 1;
   if ((c->flags & CFET_FORCE_SINGLE) && single_fits(c)) return 2;
   if ((c->flags & CFET_FORCE_COOPERATIVE) && coop_fits(c)) return 3;
@@ -334,6 +348,11 @@ int choose_path(const cfet_ctx* c) {
   if (c->n <= kAutoSingleMaxN && single_fits(c)) return 2;
   if (c->n <= kAutoCoopMaxN && coop_fits(c)) return 3;
   return 1;
+}
+
+int choose_path(const cfet_ctx* c) {
+  if (c->parity.ok && !(c->flags & (CFET_FORCE_SINGLE | CFET_FORCE_COOPERATIVE))) return 1;
+  return choose_path_csr(c);
 }
 
 int propagate_persistent(cfet_ctx* c, void* psi_dev, double t0, double dt, int64_t nsteps,
@@ -1362,10 +1381,36 @@ int cfet_create(const cfet_csr* H0, int32_t nterms, const cfet_csr* Hk, const cf
     rowlen[r] = int32_t(std::min<int64_t>(len, INT32_MAX));
     c->max_row = std::max<int>(c->max_row, rowlen[r]);
   }
-  const bool use_sell =
-      (flags & (CFET_LAYOUT_SELL | CFET_LAYOUT_SELL_UNIFORM | CFET_LAYOUT_SELL_SPLIT)) ||
-      n > kAutoCoopMaxN;
-  const bool need_csr = !use_sell || n <= kAutoCoopMaxN || (flags & CFET_KEEP_CSR);
+  // The site-operator form (parity.h) serves the automatic choice of path and
+  // layout from kParityMinN rows; a forced path or layout keeps its own
+  // kernels.  The merged CSR stays on the device up to 2^22 rows all the same
+  // (cfet_gradient runs on it).
+  const uint32_t layout_flags = CFET_LAYOUT_SELL | CFET_LAYOUT_SELL_UNIFORM | CFET_LAYOUT_SELL_SPLIT;
+  const uint32_t path_flags = CFET_FORCE_MULTIKERNEL | CFET_FORCE_SINGLE | CFET_FORCE_COOPERATIVE;
+  if (n >= kParityMinN && !(flags & layout_flags) &&
+      (n > kAutoCoopMaxN || !(flags & path_flags))) {
+    const unsigned nth = std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
+    cfet::ParityForm form;
+    if (cfet::find_parity_form(mats, nterms, n, nth, &form) &&
+        cfet::plan_parity(form, &c->parity.plan)) {
+      c->parity.ok = true;
+      c->parity.real = form.real;
+      c->parity.diag_term = form.diag_term;
+      c->parity.bytes = int64_t(form.terms.size()) * int64_t(sizeof(cfet::PElem));
+      if (form.diag_term >= 0) {
+        c->parity.bytes += 8 * n;
+        e = hipMalloc(&c->parity.diag, size_t(n) * sizeof(double));
+        if (e == hipSuccess)
+          e = hipMemcpy(c->parity.diag, form.diag.data(), size_t(n) * sizeof(double),
+                        hipMemcpyHostToDevice);
+      }
+    } else {
+      c->parity.plan = cfet::ParityPlan();
+    }
+  }
+  const bool use_sell = !c->parity.ok && ((flags & layout_flags) || n > kAutoCoopMaxN);
+  const bool need_csr =
+      !(use_sell || c->parity.ok) || n <= kAutoCoopMaxN || (flags & CFET_KEEP_CSR);
   c->A.n = n;
   c->A.nnz = nnz;
   const unsigned nth_all = std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
@@ -1375,7 +1420,8 @@ int cfet_create(const cfet_csr* H0, int32_t nterms, const cfet_csr* Hk, const cf
   // blocks each Lanczos step).  Only above the single-workgroup size, and not
   // when the multi-kernel path runs on SELL.
   std::vector<int32_t> perm, iperm;
-  if (need_csr && !use_sell && n > kAutoSingleMaxN && !(flags & CFET_NO_REORDER)) {
+  if (need_csr && !use_sell && !c->parity.ok && n > kAutoSingleMaxN &&
+      !(flags & CFET_NO_REORDER)) {
     int cus = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) ==
             hipSuccess && cus > 0) {
@@ -1398,7 +1444,7 @@ int cfet_create(const cfet_csr* H0, int32_t nterms, const cfet_csr* Hk, const cf
     }
   }
   const bool reorder = !perm.empty();
-  if (need_csr) {
+  if (e == hipSuccess && need_csr) {
     std::vector<int64_t> rp;
     std::vector<uint32_t> colt;
     std::vector<double> val;
@@ -1721,6 +1767,15 @@ int cfet_create(const cfet_csr* H0, int32_t nterms, const cfet_csr* Hk, const cf
     if (khz <= 0) khz = 100000;
     c->spin_limit = (long long)khz * 1000LL * 10LL;  // 10 s
   }
+  if (e == hipSuccess && c->parity.ok) {
+    c->parity.nblk = cfet::parity_grid(c->parity.plan, c->num_cus);
+    e = hipMalloc(&c->parity.part, size_t(4) * size_t(c->parity.nblk) * sizeof(double2));
+    cfet::PElem el[2 * cfet::kSweepTerms] = {};
+    cfet::parity_tables(c->parity.plan, el, c->parity.n);
+    if (e == hipSuccess) e = hipMalloc(&c->parity.e, sizeof(el));
+    if (e == hipSuccess) e = hipMemcpy(c->parity.e, el, sizeof(el), hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = cfet::parity_prepare();
+  }
   if (c->hi.nuni) c->nb_tile = cfet::tile_grid(n, c->tbits, c->num_cus);
   c->preset_single = need_csr ? cfet::persistent_choose_preset(c->max_row, n, true) : -1;
   if (e == hipSuccess && c->num_cus > 0 && need_csr) {
@@ -1812,7 +1867,10 @@ int cfet_apply(cfet_ctx* c, const void* x_dev, void* y_dev, double a, const doub
   for (int k = 0; k < c->nterms; ++k) tw.w[k + 1] = b[k];
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   hipError_t e;
-  if (c->use_sell && c->hi.nuni) {
+  if (c->parity.ok) {
+    e = cfet::launch_parity_apply(c->parity, tw, static_cast<const double2*>(x_dev),
+                                  static_cast<double2*>(y_dev), cfet::ChebTerm{}, st);
+  } else if (c->use_sell && c->hi.nuni) {
     e = cfet::launch_tile_apply(c->sell, c->hi, c->tbits, c->nb_tile, c->nterms, c->tile_real,
                                 tw, static_cast<const double2*>(x_dev),
                                 static_cast<double2*>(y_dev), st);
@@ -1866,8 +1924,10 @@ int run_multi(cfet_ctx* c, double t0, double dt, int64_t nsteps, const SchemeTab
   } else {
     wk.events = nullptr;
   }
-  e = cfet::launch_norm_start(W[0], c->n, c->plan, partA, st);
-  if (e != hipSuccess) return hip_fail(c, e, "norm kernel");
+  if (!c->parity.ok) {
+    e = cfet::launch_norm_start(W[0], c->n, c->plan, partA, st);
+    if (e != hipSuccess) return hip_fail(c, e, "norm kernel");
+  }
   double a[cfet::kMaxStages], b[cfet::kMaxStages * cfet::kMaxTerms];
   cfet::TermWeights tw;
   std::memset(&tw, 0, sizeof(tw));
@@ -1877,7 +1937,12 @@ int run_multi(cfet_ctx* c, double t0, double dt, int64_t nsteps, const SchemeTab
     for (int i = sc.s - 1; i >= 0; --i) {
       tw.w[0] = a[i];
       for (int k = 0; k < c->nterms; ++k) tw.w[k + 1] = b[i * c->nterms + k];
-      e = cfet::launch_exponential(c->A, c->nterms, c->plan, tw, dt, m, wk, st);
+      if (c->parity.ok) {
+        e = cfet::launch_parity_lanczos(c->parity, tw, dt, m, W, S, c->stats, wk.events, st);
+        if (e == hipSuccess) e = cfet::launch_combine(c->n, c->plan, wk, st);
+      } else {
+        e = cfet::launch_exponential(c->A, c->nterms, c->plan, tw, dt, m, wk, st);
+      }
       if (e != hipSuccess) return hip_fail(c, e, "exponential kernels");
     }
   }
@@ -1967,9 +2032,13 @@ int run_cheb(cfet_ctx* c, double t0, double dt, int64_t nsteps, const SchemeTabl
         const bool ev = timed && c->events.used < c->events.cap;
         const double scale = (k == 1 ? 1.0 : 2.0) / h;
         if (ev) (void)hipEventRecord(c->events.begin[c->events.used], st);
-        if (c->use_sell && c->hi.nuni) {
+        const cfet::ChebTerm ct{prev, psi, scale, sigma, coef(k), k == 1 ? 1 : 0};
+        if (c->parity.ok) {
+          // as on the split layout, the term is applied in the second sweep
+          e = cfet::launch_parity_apply(c->parity, tw, cur, y, ct, st);
+          if (e != hipSuccess) return hip_fail(c, e, "Chebyshev apply");
+        } else if (c->use_sell && c->hi.nuni) {
           // split layout: the term is applied in the second pass's epilogue
-          const cfet::ChebTerm ct{prev, psi, scale, sigma, coef(k), k == 1 ? 1 : 0};
           e = cfet::launch_tile_cheb(c->sell, c->hi, c->tbits, c->nb_tile, c->nterms,
                                      c->tile_real, tw, cur, y, ct, st);
           if (e != hipSuccess) return hip_fail(c, e, "Chebyshev apply");
@@ -1981,7 +2050,7 @@ int run_cheb(cfet_ctx* c, double t0, double dt, int64_t nsteps, const SchemeTabl
           (void)hipEventRecord(c->events.end[c->events.used], st);
           c->events.used += 1;
         }
-        if (!(c->use_sell && c->hi.nuni)) {
+        if (!c->parity.ok && !(c->use_sell && c->hi.nuni)) {
           e = cfet::launch_cheb_update(y, cur, prev, psi, c->n, scale, sigma, k == 1, coef(k), st);
           if (e != hipSuccess) return hip_fail(c, e, "Chebyshev update");
         }
@@ -2246,7 +2315,7 @@ int cfet_gradient(cfet_ctx* c, const void* psi0_dev, const void* target_dev, dou
   // the backward sweep then runs no Lanczos recurrence from psi.  That store
   // takes seg * s * m vectors; above kGradStoreMax (or half the free device
   // memory) the recurrence from psi is rerun instead, with the same result.
-  const int rpath = choose_path(c);
+  const int rpath = choose_path_csr(c);
   const size_t ystore = size_t(seg) * size_t(sc.s) * size_t(m) * nn * sizeof(double2);
   bool keep = rpath != 1 && c->nterms == 1 && ystore <= kGradStoreMax;
   if (keep) {
@@ -2634,9 +2703,9 @@ int cfet_stats(cfet_ctx* c, cfet_stats_t* s) {
   s->min_m_eff = d.exponentials ? d.min_m_eff : 0;
   s->breakdowns = d.breakdowns;
   s->path = c->last_path;
-  s->layout = !c->use_sell ? 0 : (c->hi.nuni ? 3 : (c->sell.nuni ? 2 : 1));
+  s->layout = (c->parity.ok && c->n > kAutoCoopMaxN) ? 3 : !c->use_sell ? 0 : (c->hi.nuni ? 3 : (c->sell.nuni ? 2 : 1));
   s->reordered = c->perm ? 1 : 0;
-  s->matrix_bytes = c->use_sell ? c->sell_bytes : 20 * c->A.nnz + 8 * (c->n + 1);
+  s->matrix_bytes = c->parity.ok ? c->parity.bytes : c->use_sell ? c->sell_bytes : 20 * c->A.nnz + 8 * (c->n + 1);
   s->status = d.status;
   s->last_norm = std::sqrt(d.last_norm2);
   harvest_events(c);

@@ -356,9 +356,10 @@ __global__ __launch_bounds__(64) void k_lz_small(const double* __restrict__ part
   }
 }
 
-// basis vector j >= 1 lives at basis + (j-1)*n; vector 0 is psi itself
+// basis vector j >= 1 lives at basis + (j-1)*stride; vector 0 is psi itself
 __global__ __launch_bounds__(kBlock) void k_lz_combine(double2* __restrict__ psi,
-                                                       const double2* __restrict__ basis, int64_t n,
+                                                       const double2* __restrict__ basis,
+                                                       int64_t stride_v, int64_t n,
                                                        const LzScalars* __restrict__ S,
                                                        double* __restrict__ part_out) {
   __shared__ double red[17];
@@ -375,7 +376,7 @@ __global__ __launch_bounds__(kBlock) void k_lz_combine(double2* __restrict__ psi
     typedef double dv2 __attribute__((ext_vector_type(2)));
     for (int jj = 0; jj < meff; ++jj) {
       const dv2* src = (jj == 0) ? reinterpret_cast<const dv2*>(psi) + r
-                                 : reinterpret_cast<const dv2*>(basis) + (int64_t)(jj - 1) * n + r;
+                                 : reinterpret_cast<const dv2*>(basis) + (int64_t)(jj - 1) * stride_v + r;
       const dv2 v = __builtin_nontemporal_load(src);
       const double2 k = cf[jj];
       accr += k.x * v.x - k.y * v.y;
@@ -547,8 +548,9 @@ hipError_t launch_lanczos(const DevCSR& A, int nterms, const LaunchPlan& plan,
 }
 
 hipError_t launch_combine(int64_t n, const LaunchPlan& plan, const ExpWork& wk, hipStream_t st) {
+  const int64_t stride = wk.W_host[2] ? wk.W_host[2] - wk.W_host[1] : n;
   hipLaunchKernelGGL(k_lz_combine, dim3(plan.nb_vec), dim3(kBlock), 0, st, wk.W_host[0],
-                     (const double2*)wk.W_host[1], n, wk.S, wk.partA);
+                     (const double2*)wk.W_host[1], stride, n, wk.S, wk.partA);
   return hipGetLastError();
 }
 

@@ -1,0 +1,118 @@
+// Site-operator form of a merged operator and the two-sweep kernels on it.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+#include <vector>
+
+#include "cfet_internal.h"
+#include "host_common.h"
+
+namespace cfet {
+
+// One off-diagonal term of an operator on 2^nb rows: row r couples to column
+// r XOR off with a value that depends on one parity of the row's bits only,
+//     v(r) = parity(r & pmask) ? v1 : v0
+// (0 where the operator stores nothing).  Every Pauli string and the sums of
+// strings with the same flips have this form: sigma^x (pmask = 0), sigma^y
+// (pmask = off, v1 = -v0 imaginary), a flip-flop s+s- + s-s+ of two sites
+// (pmask = off, v0 = 0).
+struct ParityTerm {
+  uint32_t off, pmask;
+  int term;  // 0: H0, 1 + k: H_k
+  double v0[2], v1[2];
+};
+
+struct ParityForm {
+  int nb = 0;                      // rows = 2^nb
+  std::vector<ParityTerm> terms;   // off-diagonal part
+  int diag_term = -1;              // term that holds the diagonal (-1: none)
+  std::vector<double> diag;        // real diagonal, one value per row
+  bool real = true;                // every value is real
+};
+
+// The form of the merged operator, or false: the rows are not a power of two,
+// an entry's values follow no parity, the diagonal is complex or lies in more
+// than one term, or there are more than kParityMaxTerms off-diagonal terms.
+// Exact: every stored value is compared with what the form says, bit for bit.
+constexpr int kParityMaxTerms = 56;
+constexpr int kSweepTerms = 64;  // with the padding of the sweeps' groups
+bool find_parity_form(const std::vector<HostCSR>& mats, int nterms, int64_t n, unsigned nth,
+                      ParityForm* F);
+
+// The plan of the two sweeps.  The second sweep walks tiles of 2^tbl
+// consecutive rows and applies every term whose flips stay inside the tile.
+// The first walks tiles of a permuted order whose index bits are the `low`
+// lowest row bits (contiguous segments of a vector), then the row bits from
+// `high` up, then those between; it applies the terms that flip high bits.  A
+// term that fits neither is gathered from memory in the second sweep.
+struct ParityPlan {
+  int nb = 0;
+  int tbh = 0, tbl = 0;            // tile bits of the first and of the second sweep
+  int low = 0, high = 0;           // tbh = low + nb - high
+  std::vector<ParityTerm> hi, lo, far;
+};
+constexpr int kParityMinBits = 14;
+constexpr int kParityMaxBits = 27;  // byte offsets inside a vector fit 32 bits
+bool plan_parity(const ParityForm& F, ParityPlan* P);
+
+// One term as a sweep reads it (device memory, 48 bytes).
+struct PElem {
+  uint32_t off;    // XOR on the tile index (gathered terms: on the row)
+  uint32_t pmask;  // parity mask on the row
+  uint32_t rpar;   // bit r: parity of the mask over the row bits of register r
+  int32_t term;    // 0: H0, 1 + k: H_k
+  double v0, v1;   // real parts
+  double w0, w1;   // imaginary parts
+};
+
+struct SweepArgs {
+  const PElem* e;           // the sweep's terms, in five groups (parity.hip) of n[0] .. n[4]
+  int n[5];
+  int nb, tb, low, high;
+  int k, m;                 // Lanczos phase and Krylov size (recurrence only)
+  int nblk;
+  const double2* x;         // the vector multiplied (recurrence: u_{k-1} in the first sweep)
+  double2* u;               // recurrence, first sweep: z_{k-1} in, u_k out
+  const double2* u2;        // u_{k-2}
+  double2* y;               // result: the first sweep writes its part, the second adds to it
+  const double* diag;
+  LzScalars* S;
+  const double2* part_in;   // the last phase's records: first sweep [0, nblk), second [nblk, 2 nblk)
+  double2* part_out;
+  double wdiag;
+  TermWeights tw;
+  ChebTerm ct;
+};
+
+// Device side of a context's site-operator form.
+struct DevParity {
+  bool ok = false;
+  ParityPlan plan;
+  bool real = true;
+  int diag_term = -1;
+  double* diag = nullptr;   // device
+  PElem* e = nullptr;       // device: first sweep's terms, second sweep's
+  int n[2][5] = {};         // their group sizes
+  double2* part = nullptr;  // device: 2 sets x 2 sweeps x nblk records
+  int nblk = 0;
+  int64_t bytes = 0;        // operator bytes one application reads
+};
+
+int parity_grid(const ParityPlan& P, int num_cus);
+hipError_t parity_prepare();
+// The terms of the two sweeps in the kernels' order and groups (host; sweep 0,
+// 1 at e + sweep * kSweepTerms).
+void parity_tables(const ParityPlan& P, PElem* e, int n[2][5]);
+// y = H_w x (x and y distinct); with ct.psi set, the Chebyshev term instead
+// of the store of y (y is then scratch).
+hipError_t launch_parity_apply(const DevParity& P, const TermWeights& tw, const double2* x,
+                               double2* y, const ChebTerm& ct, hipStream_t st);
+// The Lanczos recurrence from W[0] with the small exponential (basis W[1..],
+// unnormalised, scalars S): the contract of launch_lanczos.
+hipError_t launch_parity_lanczos(const DevParity& P, const TermWeights& tw, double dt, int m,
+                                 double2* const* W, LzScalars* S, DevStats* stats,
+                                 EventPool* events, hipStream_t st);
+
+}  // namespace cfet
