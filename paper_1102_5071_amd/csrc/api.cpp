@@ -36,6 +36,7 @@ struct cfet_ctx {
   bool tile_real = false;   // every value stored in the split layout is real
   bool use_sell = false;
   cfet::DevParity parity;   // site-operator form (parity.ok: the products run on it)
+  cfet::DevSite site;       // the same for the persistent paths (site.ok)
   int64_t sell_bytes = 0;   // stored SELL data one application reads
   // row order of the CSR paths (null: the caller's): row i of the stored
   // operator is the caller's row perm[i], caller row j is row iperm[j];
@@ -214,6 +215,10 @@ void free_ctx(cfet_ctx* c) {
   if (c->sell.cval) (void)hipFree(c->sell.cval);
   if (c->hi.ccolt) (void)hipFree(c->hi.ccolt);
   if (c->hi.cval) (void)hipFree(c->hi.cval);
+  if (c->site.diag) (void)hipFree(c->site.diag);
+  if (c->site.e) (void)hipFree(c->site.e);
+  if (c->site.rec) (void)hipFree(c->site.rec);
+  if (c->site.ids) (void)hipFree(c->site.ids);
   if (c->parity.diag) (void)hipFree(c->parity.diag);
   if (c->parity.e) (void)hipFree(c->parity.e);
   if (c->parity.part) (void)hipFree(c->parity.part);
@@ -341,6 +346,7 @@ bool coop_fits(const cfet_ctx* c) { return c->preset_coop >= 0 && c->coop_blocks
 // The path of the persistent kernels' callers (cfet_gradient): without the
 // sweeps on the site-operator form, which only propagation uses.
 int choose_path_csr(const cfet_ctx* c) {
+  if (c->site.ok) return c->site.plan.blocks == 1 ? 2 : 3;
   if (c->flags & CFET_FORCE_MULTIKERNEL) return 1;
   if ((c->flags & CFET_FORCE_SINGLE) && single_fits(c)) return 2;
   if ((c->flags & CFET_FORCE_COOPERATIVE) && coop_fits(c)) return 3;
@@ -351,7 +357,7 @@ int choose_path_csr(const cfet_ctx* c) {
 }
 
 int choose_path(const cfet_ctx* c) {
-  if (c->parity.ok && !(c->flags & (CFET_FORCE_SINGLE | CFET_FORCE_COOPERATIVE))) return 1;
+  if (c->parity.ok && !c->site.ok) return 1;
   return choose_path_csr(c);
 }
 
@@ -408,7 +414,7 @@ int propagate_persistent(cfet_ctx* c, void* psi_dev, double t0, double dt, int64
   if (e != hipSuccess) return hip_fail(c, e, "upload the weight table");
   c->wts_pending = true;
   int nblocks = 1;
-  if (path == 3) {
+  if (path == 3 && !c->site.ok) {
     nblocks = c->coop_blocks;
     if (4 * nblocks > c->part_cap) {
       if (c->d_part) (void)hipFree(c->d_part);
@@ -458,8 +464,9 @@ int propagate_persistent(cfet_ctx* c, void* psi_dev, double t0, double dt, int64
   pa.export_each = (export_T || export_Y) ? 1 : 0;
   const bool timed = c->profiling && c->events.used < c->events.cap;
   if (timed) (void)hipEventRecord(c->events.begin[c->events.used], st);
-  e = cfet::launch_persistent(pa, path == 2 ? c->preset_single : c->preset_coop, path == 2,
-                             nblocks, st);
+  e = c->site.ok ? cfet::launch_site(c->site, pa, st)
+                 : cfet::launch_persistent(pa, path == 2 ? c->preset_single : c->preset_coop,
+                                           path == 2, nblocks, st);
   if (timed && e == hipSuccess) {
     (void)hipEventRecord(c->events.end[c->events.used], st);
     c->events.used += 1;
@@ -509,9 +516,11 @@ hipError_t persistent_exponential(cfet_ctx* c, int path, double2* psi, double2* 
   if (bar) pa.bar = bar;  // cleared by the caller on the stream
   const bool timed = c->profiling && c->events.used < c->events.cap;
   if (timed) (void)hipEventRecord(c->events.begin[c->events.used], st);
-  const hipError_t e = cfet::launch_persistent(pa, path == 2 ? c->preset_single : c->preset_coop,
-                                               path == 2, path == 3 ? c->coop_blocks : 1, st,
-                                               bar == nullptr);
+  const hipError_t e =
+      c->site.ok ? cfet::launch_site(c->site, pa, st)
+                 : cfet::launch_persistent(pa, path == 2 ? c->preset_single : c->preset_coop,
+                                           path == 2, path == 3 ? c->coop_blocks : 1, st,
+                                           bar == nullptr);
   if (timed && e == hipSuccess) {
     (void)hipEventRecord(c->events.end[c->events.used], st);
     c->events.used += 1;
@@ -1387,25 +1396,44 @@ int cfet_create(const cfet_csr* H0, int32_t nterms, const cfet_csr* Hk, const cf
   // (cfet_gradient runs on it).
   const uint32_t layout_flags = CFET_LAYOUT_SELL | CFET_LAYOUT_SELL_UNIFORM | CFET_LAYOUT_SELL_SPLIT;
   const uint32_t path_flags = CFET_FORCE_MULTIKERNEL | CFET_FORCE_SINGLE | CFET_FORCE_COOPERATIVE;
-  if (n >= kParityMinN && !(flags & layout_flags) &&
-      (n > kAutoCoopMaxN || !(flags & path_flags))) {
-    const unsigned nth = std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
+  if (!(flags & layout_flags) && (n > kAutoCoopMaxN || !(flags & path_flags))) {
+    const unsigned nth =
+        n < 65536 ? 1u : std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
     cfet::ParityForm form;
-    if (cfet::find_parity_form(mats, nterms, n, nth, &form) &&
-        cfet::plan_parity(form, &c->parity.plan)) {
+    const bool found = cfet::find_parity_form(mats, nterms, n, nth, &form);
+    auto upload_diag = [&](double** d) {
+      if (form.diag_term < 0 || e != hipSuccess) return;
+      e = hipMalloc(d, size_t(n) * sizeof(double));
+      if (e == hipSuccess)
+        e = hipMemcpy(*d, form.diag.data(), size_t(n) * sizeof(double), hipMemcpyHostToDevice);
+    };
+    if (found && cfet::plan_site(form, &c->site.plan)) {
+      int cus = 0;
+      bool fits = false;
+      e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device);
+      if (e == hipSuccess) e = cfet::site_prepare(c->site.plan, form.real, cus, &fits);
+      if (e == hipSuccess && fits) {
+        c->site.ok = true;
+        c->site.real = form.real;
+        c->site.diag_term = form.diag_term;
+        upload_diag(&c->site.diag);
+        if (e == hipSuccess) e = hipMalloc(&c->site.e, sizeof(c->site.plan.e));
+        if (e == hipSuccess)
+          e = hipMemcpy(c->site.e, c->site.plan.e, sizeof(c->site.plan.e), hipMemcpyHostToDevice);
+        if (e == hipSuccess) e = hipMalloc(&c->site.rec, 3 * cfet::kSiteRecs * 16);
+        if (e == hipSuccess) e = hipMemset(c->site.rec, 0, 3 * cfet::kSiteRecs * 16);
+        if (e == hipSuccess) e = hipMalloc(&c->site.ids, 257 * sizeof(unsigned long long));
+        if (e == hipSuccess) e = hipMemset(c->site.ids, 0, 257 * sizeof(unsigned long long));
+        c->site.count = c->site.ids + 256;
+      }
+    }
+    if (found && n >= kParityMinN && cfet::plan_parity(form, &c->parity.plan)) {
       c->parity.ok = true;
       c->parity.real = form.real;
       c->parity.diag_term = form.diag_term;
-      c->parity.bytes = int64_t(form.terms.size()) * int64_t(sizeof(cfet::PElem));
-      if (form.diag_term >= 0) {
-        c->parity.bytes += 8 * n;
-        e = hipMalloc(&c->parity.diag, size_t(n) * sizeof(double));
-        if (e == hipSuccess)
-          e = hipMemcpy(c->parity.diag, form.diag.data(), size_t(n) * sizeof(double),
-                        hipMemcpyHostToDevice);
-      }
-    } else {
-      c->parity.plan = cfet::ParityPlan();
+      c->parity.bytes = int64_t(form.terms.size()) * int64_t(sizeof(cfet::PElem)) +
+                        (form.diag_term >= 0 ? 8 * n : 0);
+      upload_diag(&c->parity.diag);
     }
   }
   const bool use_sell = !c->parity.ok && ((flags & layout_flags) || n > kAutoCoopMaxN);
@@ -1420,7 +1448,7 @@ int cfet_create(const cfet_csr* H0, int32_t nterms, const cfet_csr* Hk, const cf
   // blocks each Lanczos step).  Only above the single-workgroup size, and not
   // when the multi-kernel path runs on SELL.
   std::vector<int32_t> perm, iperm;
-  if (need_csr && !use_sell && !c->parity.ok && n > kAutoSingleMaxN &&
+  if (need_csr && !use_sell && !c->parity.ok && !c->site.ok && n > kAutoSingleMaxN &&
       !(flags & CFET_NO_REORDER)) {
     int cus = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) ==

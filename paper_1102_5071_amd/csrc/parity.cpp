@@ -97,6 +97,7 @@ bool find_parity_form(const std::vector<HostCSR>& mats, int nterms, int64_t n, u
   while ((int64_t(1) << nb) < n) ++nb;
   if ((int64_t(1) << nb) != n || nb > kParityMaxBits) return false;
   F->nb = nb;
+  F->nterms = nterms;
   // a first look at a few rows turns most other operators away at once
   for (int64_t r = 0; r < n; r += std::max<int64_t>(1, n / 8)) {
     int64_t len = 0;
@@ -268,6 +269,27 @@ void tiles_of(int nb, int* tbh, int* tbl, int* low) {
 
 }  // namespace
 
+std::vector<ParityTerm> merge_terms(const std::vector<ParityTerm>& terms) {
+  std::vector<ParityTerm> out;
+  for (const ParityTerm& t : terms) {
+    bool done = false;
+    for (ParityTerm& o : out) {
+      if (o.off != t.off || o.term == t.term || o.term2 >= 0) continue;
+      if (o.pmask != t.pmask && o.pmask != 0 && t.pmask != 0) continue;
+      if (o.pmask == 0) o.pmask = t.pmask;
+      o.term2 = t.term;
+      for (int c = 0; c < 2; ++c) {
+        o.b0[c] = t.v0[c];
+        o.b1[c] = t.v1[c];
+      }
+      done = true;
+      break;
+    }
+    if (!done) out.push_back(t);
+  }
+  return out;
+}
+
 bool plan_parity(const ParityForm& F, ParityPlan* P) {
   const int nb = F.nb;
   if (nb < kParityMinBits) return false;
@@ -283,14 +305,15 @@ bool plan_parity(const ParityForm& F, ParityPlan* P) {
   P->low = low;
   P->high = s;
   const uint32_t himask = (~0u << s) | ((1u << low) - 1u);
-  for (const ParityTerm& t : F.terms) {
+  const std::vector<ParityTerm> terms = merge_terms(F.terms);
+  for (const ParityTerm& t : terms) {
     if ((t.off >> tbl) == 0) P->lo.push_back(t);
     else if ((t.off & ~himask) == 0) P->hi.push_back(t);
     else P->far.push_back(t);
   }
   // gathered terms cost a read of the vector from beyond the tile each: more
   // than a quarter of the terms and the other layouts serve better
-  return 4 * P->far.size() <= F.terms.size() + 3;
+  return 4 * P->far.size() <= terms.size() + 3;
 }
 
 }  // namespace cfet

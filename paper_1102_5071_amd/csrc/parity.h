@@ -22,10 +22,15 @@ struct ParityTerm {
   uint32_t off, pmask;
   int term;  // 0: H0, 1 + k: H_k
   double v0[2], v1[2];
+  // a second operator term's part with the same flips (-1: none), on the same
+  // mask; see merge_terms
+  int term2 = -1;
+  double b0[2] = {0.0, 0.0}, b1[2] = {0.0, 0.0};
 };
 
 struct ParityForm {
   int nb = 0;                      // rows = 2^nb
+  int nterms = 0;                  // driven terms
   std::vector<ParityTerm> terms;   // off-diagonal part
   int diag_term = -1;              // term that holds the diagonal (-1: none)
   std::vector<double> diag;        // real diagonal, one value per row
@@ -40,6 +45,11 @@ constexpr int kParityMaxTerms = 56;
 constexpr int kSweepTerms = 64;  // with the padding of the sweeps' groups
 bool find_parity_form(const std::vector<HostCSR>& mats, int nterms, int64_t n, unsigned nth,
                       ParityForm* F);
+
+// Terms of different operator terms with the same flips as one, where one of
+// the two has a single value or both the same mask (sigma^x and sigma^y of a
+// site): the kernels read x once for both.
+std::vector<ParityTerm> merge_terms(const std::vector<ParityTerm>& terms);
 
 // The plan of the two sweeps.  The second sweep walks tiles of 2^tbl
 // consecutive rows and applies every term whose flips stay inside the tile.
@@ -57,7 +67,7 @@ constexpr int kParityMinBits = 14;
 constexpr int kParityMaxBits = 27;  // byte offsets inside a vector fit 32 bits
 bool plan_parity(const ParityForm& F, ParityPlan* P);
 
-// One term as a sweep reads it (device memory, 48 bytes).
+// One term as a kernel reads it (device memory).
 struct PElem {
   uint32_t off;    // XOR on the tile index (gathered terms: on the row)
   uint32_t pmask;  // parity mask on the row
@@ -65,7 +75,29 @@ struct PElem {
   int32_t term;    // 0: H0, 1 + k: H_k
   double v0, v1;   // real parts
   double w0, w1;   // imaginary parts
+  int32_t term2;   // second part (ParityTerm), 0 with zero values where there is none
+  int32_t pad;
+  double b0, b1;
+  double d0, d1;
 };
+// (off and rpar are the caller's)
+inline PElem make_elem(const ParityTerm& t) {
+  PElem e{};
+  e.pmask = t.pmask;
+  e.term = t.term;
+  e.v0 = t.v0[0];
+  e.v1 = t.v1[0];
+  e.w0 = t.v0[1];
+  e.w1 = t.v1[1];
+  if (t.term2 >= 0) {
+    e.term2 = t.term2;
+    e.b0 = t.b0[0];
+    e.b1 = t.b1[0];
+    e.d0 = t.b0[1];
+    e.d1 = t.b1[1];
+  }
+  return e;
+}
 
 struct SweepArgs {
   const PElem* e;           // the sweep's terms, in five groups (parity.hip) of n[0] .. n[4]
@@ -114,5 +146,49 @@ hipError_t launch_parity_apply(const DevParity& P, const TermWeights& tw, const 
 hipError_t launch_parity_lanczos(const DevParity& P, const TermWeights& tw, double dt, int m,
                                  double2* const* W, LzScalars* S, DevStats* stats,
                                  EventPool* events, hipStream_t st);
+
+// ---- persistent propagation on the same form (site.hip)
+//
+// One workgroup up to 2^10 rows; above, a team of workgroups on one XCD, each
+// with 2^tl consecutive rows (T threads times R rows).
+constexpr int kSiteRecs = 64;   // records of one exchange: two per block of a team
+constexpr int kSiteSlots = 64;  // terms of a plan, at most
+struct SitePlan {
+  int blocks = 0, T = 0, R = 0, tl = 0;
+  int mode = 0;              // SiteMode (site.hip)
+  int set_term[2] = {0, 0};  // operator term of each set
+  int nfar[2] = {0, 0};      // terms that leave the block, per set
+  PElem e[kSiteSlots] = {};  // by slot
+};
+bool plan_site(const ParityForm& F, SitePlan* P);
+
+struct DevSite {
+  bool ok = false;
+  SitePlan plan;
+  bool real = true;
+  int diag_term = -1;
+  double* diag = nullptr;             // device (null: no diagonal)
+  PElem* e = nullptr;                 // device
+  void* rec = nullptr;                // device: 3 * kSiteRecs records
+  unsigned long long* ids = nullptr;  // device: XCD of each block of a launch, then the launch counter
+  unsigned long long* count = nullptr;
+};
+
+struct SiteArgs {
+  PersistArgs p;
+  const PElem* e;
+  int nfar[2], set_term[2];
+  const double* diag;
+  int diag_term;
+  int tl, blocks;
+  void* rec;
+  unsigned long long* ids;
+  unsigned long long* count;
+};
+
+// Sets up the plan's kernel; *fits: a launch's blocks are co-resident.
+hipError_t site_prepare(const SitePlan& P, bool real, int num_cus, bool* fits);
+// A whole call (see PersistArgs; basis, psi, wts and the exports are used).
+hipError_t launch_site(const DevSite& S, const PersistArgs& args, hipStream_t st);
 
 }  // namespace cfet

@@ -23,41 +23,15 @@
 #include <type_traits>
 
 #include "parity.h"
+#include "sweep_common.hpp"
 #include "tridiag.hpp"
 
 namespace cfet {
 
 namespace {
 
-typedef double dv2 __attribute__((ext_vector_type(2)));
-typedef __attribute__((address_space(3))) const dv2* lds_cptr;
-
 // what a launch computes
 enum SweepOp { kApply = 0, kLanczos = 1, kCheb = 2 };
-
-__device__ __forceinline__ double2 lds_at(uint32_t byte_addr) {
-  const dv2 v = *(lds_cptr)(uintptr_t)byte_addr;
-  return make_double2(v.x, v.y);
-}
-
-// One DPP step of the wavefront sum: v + (v moved by the DPP pattern), rows
-// outside the row mask add 0.
-template <int CTRL, int ROWMASK>
-__device__ __forceinline__ double w_step(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWMASK, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWMASK, 0xf, false);
-  return v + __hiloint2double(hi, lo);
-}
-
-// Sum over the 64 lanes in a fixed order; lane 63 holds it.
-__device__ __forceinline__ double w_sum63(double v) {
-  v = w_step<0xB1, 0xf>(v);   // quad_perm [1,0,3,2]
-  v = w_step<0x4E, 0xf>(v);   // quad_perm [2,3,0,1]
-  v = w_step<0x141, 0xf>(v);  // row_half_mirror
-  v = w_step<0x140, 0xf>(v);  // row_mirror
-  v = w_step<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
-  return w_step<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
-}
 
 // Sums of a and b over the block, in wavefront order; every thread gets them.
 template <int T>
@@ -174,17 +148,6 @@ __device__ __forceinline__ dv2 value_of(const E& e, uint32_t p) {
   return v;
 }
 
-template <bool RV>
-__device__ __forceinline__ void acc_fma(double2& acc, dv2 v, double2 x) {
-  if (RV) {
-    acc.x = fma(v.x, x.x, acc.x);
-    acc.y = fma(v.x, x.y, acc.y);
-  } else {
-    acc.x = fma(v.x, x.x, fma(-v.y, x.y, acc.x));
-    acc.y = fma(v.x, x.y, fma(v.y, x.x, acc.y));
-  }
-}
-
 // Element of a vector at a wavefront-uniform row plus the thread's own byte
 // offset (32 bits: nb <= kParityMaxBits): one scalar base per access and one
 // vector register for all of them.
@@ -221,6 +184,7 @@ struct WElem {
   double w0, w1;
 };
 
+// terms whose tile reads are in flight together, for R rows per thread
 constexpr int batch_of(int R) { return R <= 2 ? 4 : R == 4 ? 2 : 1; }
 
 template <int TB, int T, bool RV, bool HI, int OP, bool NTL>
@@ -324,10 +288,15 @@ __global__ __launch_bounds__(T, RV || T > 512 ? 4 : 2) void k_sweep(SweepArgs A)
         }
       }
       if (t < n4) {
-        double w = A.tw.w[0];
+        double w = A.tw.w[0], w2 = A.tw.w[0];
 #pragma unroll
-        for (int k = 1; k <= kMaxTerms; ++k) w = e.term == k ? A.tw.w[k] : w;
-        we[t] = {e.off, e.pmask, e.rpar, 0u, w * e.v0, w * e.v1, w * e.w0, w * e.w1};
+        for (int k = 1; k <= kMaxTerms; ++k) {
+          w = e.term == k ? A.tw.w[k] : w;
+          w2 = e.term2 == k ? A.tw.w[k] : w2;
+        }
+        we[t] = {e.off, e.pmask, e.rpar, 0u,
+                 fma(w2, e.b0, w * e.v0), fma(w2, e.b1, w * e.v1),
+                 fma(w2, e.d0, w * e.w0), fma(w2, e.d1, w * e.w1)};
       }
     } else {
       __syncthreads();  // the previous tile's readers are done
@@ -637,14 +606,8 @@ void parity_tables(const ParityPlan& P, PElem* out, int n[2][5]) {
       return hi ? (off & ((1u << P.low) - 1u)) | ((off >> P.high) << P.low) : off;
     };
     auto element = [&](const ParityTerm& t, bool gather, int* group) {
-      PElem e{};
+      PElem e = make_elem(t);
       e.off = gather ? t.off : local(t.off);
-      e.pmask = t.pmask;
-      e.term = t.term;
-      e.v0 = t.v0[0];
-      e.v1 = t.v1[0];
-      e.w0 = t.v0[1];
-      e.w1 = t.v1[1];
       for (int r = 0; r < R; ++r)
         e.rpar |= uint32_t(__builtin_popcount(row_of(uint32_t(r * T)) & t.pmask) & 1) << r;
       const bool thread_flip = (e.off & uint32_t(T - 1)) != 0;

@@ -1,0 +1,158 @@
+"""The persistent kernels on the site-operator form (one workgroup up to 2^10
+rows, a team of workgroups up to 2^14) against the CPU oracle, at every
+launch shape: fewer rows than a wavefront, one row per thread, several, teams
+of 8 to 32 blocks with one, two and four rows per thread.
+
+Bars: propagation 1e-10 and the oracle's number of H applications; gradient as
+in the gradient tests (1e-8 of its largest entry).
+"""
+import numpy as np
+import pytest
+
+from oracle import adjoint as A
+from oracle import cfet as O
+from paper_1102_5071_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+B = pytest.importorskip("paper_1102_5071_amd.binding")
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU")
+    B.load()
+    yield
+    torch.cuda.synchronize()
+
+
+def dev(v):
+    return torch.from_numpy(np.ascontiguousarray(v, dtype=np.complex128)).to("cuda")
+
+
+def rel(a, b):
+    return np.linalg.norm(a - b) / np.linalg.norm(b)
+
+
+def chain(model, L, seed):
+    rng = np.random.default_rng(seed)
+    if model == "spins":                       # two drives, complex values
+        H0, Hk, drives = I.noninteracting_spins(L, 0.3, 0.7, 1.1)
+    elif model == "y":                         # one drive with complex values
+        H0, Hk = I.heisenberg_chain(L, 1.0, rng.uniform(-1, 1, L)), [I.sigma_y_sum(L)]
+        drives = [{"kind": "cos", "A": 0.8, "omega": 2.0, "phi": 0.3}]
+    elif model == "driven_diag":               # the diagonal is the driven term
+        H0 = I.sigma_x_sum(L, rng.uniform(0.5, 1.5, L))
+        Hk = [I.ising_chain(L, 1.0, rng.uniform(-1, 1, L))]
+        drives = [{"kind": "cos", "A": 0.8, "omega": 2.0, "phi": 0.3}]
+    else:
+        H0 = (I.heisenberg_chain if model == "heisenberg" else I.ising_chain)(
+            L, 1.0, rng.uniform(-1, 1, L))
+        Hk = [I.sigma_x_sum(L)]
+        drives = [{"kind": "cos", "A": 0.8, "omega": 2.0, "phi": 0.3}]
+    return H0, Hk, drives, I.random_state(1 << L, rng)
+
+
+@pytest.mark.parametrize("L", list(range(1, 17)))
+@pytest.mark.parametrize("model", ["ising", "heisenberg", "spins", "y", "driven_diag"])
+def test_propagate_matches_oracle(model, L):
+    if model == "heisenberg" and L == 1:
+        pytest.skip("a chain of one site has no bond")
+    H0, Hk, drives, psi0 = chain(model, L, 10 * L)
+    steps, m = (3, 12) if L < 14 else (1, 10)
+    scheme = "CF6:5Opt" if L < 12 else "CF4:2"
+    stats = {}
+    ref = O.propagate(H0, Hk, drives, psi0, 0.1, 0.04, steps, scheme, m=m, stats=stats)
+    with B.Propagator(H0, Hk, drives) as P:
+        psi = dev(psi0)
+        P.propagate(psi, 0.1, 0.04, steps, scheme, m)
+        st = P.stats()
+        out = psi.cpu().numpy()
+        again = dev(psi0)
+        P.propagate(again, 0.1, 0.04, steps, scheme, m)
+        assert torch.equal(again, psi)          # fixed order of every sum
+    assert st["status"] == 0
+    assert B.PATH_NAMES[st["path"]] == ("single" if L <= 10 else "coop" if L <= 15 else "multi")
+    assert st["matvecs"] == stats["n_matvec"]
+    assert abs(st["last_norm"] - 1.0) < 1e-10
+    assert rel(out, ref) <= 1e-10
+
+
+@pytest.mark.parametrize("L,m", [(4, 64), (9, 64), (12, 1), (12, 2), (13, 40), (5, 3)])
+def test_krylov_sizes(L, m):
+    H0, Hk, drives, psi0 = chain("heisenberg", L, L + m)
+    dt = 0.02 if m > 3 else 1e-4
+    ref = O.propagate(H0, Hk, drives, psi0, 0.0, dt, 2, "CF4:2", m=m)
+    with B.Propagator(H0, Hk, drives) as P:
+        psi = dev(psi0)
+        P.propagate(psi, 0.0, dt, 2, "CF4:2", m)
+        assert P.stats()["status"] == 0
+        assert rel(psi.cpu().numpy(), ref) <= 1e-10
+
+
+@pytest.mark.parametrize("L", [7, 13])
+def test_early_stop_zero_state_and_faults(L):
+    n = 1 << L
+    H0 = I.diagonal(np.full(n, 0.7))
+    plus = np.full(n, 2.0 ** (-L / 2), dtype=complex)
+    with B.Propagator(H0, [I.sigma_x_sum(L)],
+                      [{"kind": "cos", "A": 0.5, "omega": 0.0, "phi": 0.0}]) as P:
+        psi = dev(plus)
+        P.propagate(psi, 0.0, 0.2, 2, "CF4:2", 10)
+        st = P.stats()
+        out = psi.cpu().numpy()
+        assert st["status"] == 0 and st["matvecs"] == 4 and st["breakdowns"] == 4
+        assert rel(out, plus * np.exp(-0.4j * (0.7 + 0.5 * L))) < 1e-13
+        zero = dev(np.zeros(n))
+        P.propagate(zero, 0.0, 0.2, 2, "CF4:2", 10)
+        st = P.stats()
+        assert st["status"] == 0 and st["min_m_eff"] == 0 and not torch.any(zero != 0)
+        bad = dev(plus)
+        bad[n // 2] = float("nan")
+        P.propagate(bad, 0.0, 0.2, 1, "CF4:2", 10)
+        assert P.stats()["status"] != 0
+        psi = dev(plus)
+        P.propagate(psi, 0.0, 0.2, 2, "CF4:2", 10)
+        assert P.stats()["status"] == 0 and np.array_equal(psi.cpu().numpy(), out)
+
+
+@pytest.mark.parametrize("model,L", [("ising", 6), ("ising", 11), ("heisenberg", 12),
+                                     ("driven_diag", 12), ("y", 12), ("heisenberg", 15)])
+def test_gradient_matches_oracle(model, L):
+    H0, Hk, _, psi0 = chain(model, L, 3 * L)
+    rng = np.random.default_rng(L)
+    K, steps, dt = 3, (6 if L < 15 else 3), 0.05
+    u = rng.uniform(-1, 1, K)
+    drives = [{"kind": "pwc", "t_edges": np.linspace(0.0, steps * dt, K + 1), "u": u}]
+    target = I.random_state(1 << L, rng)
+    F, g = A.fidelity_gradient(H0, Hk, drives, psi0, target, 0.0, dt, steps, "CF4:2", 14)[:2]
+    with B.Propagator(H0, Hk, drives) as P:
+        Fg, gg = P.gradient(dev(psi0), dev(target), 0.0, dt, steps, "CF4:2", 14)
+    assert abs(Fg - F) <= 1e-10 * max(F, 1e-3)
+    assert np.max(np.abs(gg - g)) <= 1e-8 * np.max(np.abs(g))
+
+
+def test_two_streams_and_two_contexts():
+    # two contexts in flight on two streams, teams of 16 and 8 blocks
+    jobs = []
+    for L in (13, 12):
+        H0, Hk, drives, psi0 = chain("heisenberg", L, L)
+        P = B.Propagator(H0, Hk, drives)
+        ref = dev(psi0)
+        P.propagate(ref, 0.0, 0.05, 4, "CF6:5Opt", 16)
+        jobs.append((P, psi0, ref, torch.cuda.Stream()))
+    torch.cuda.synchronize()
+    outs = []
+    for P, psi0, ref, s in jobs:
+        psi = dev(psi0)
+        torch.cuda.synchronize()
+        outs.append(psi)
+    for (P, psi0, ref, s), psi in zip(jobs, outs):
+        for _ in range(1):
+            P.propagate(psi, 0.0, 0.05, 4, "CF6:5Opt", 16, stream=s)
+    torch.cuda.synchronize()
+    for (P, psi0, ref, s), psi in zip(jobs, outs):
+        assert P.stats()["status"] == 0 and torch.equal(psi, ref)
+        P.close()
