@@ -270,10 +270,13 @@ CFET_API int cfet_propagate_chebyshev(cfet_ctx *c, void *psi_dev, double t0, dou
  * exponential: the top-right block of exp([[Omega, D], [0, Omega]]), taken by
  * projecting that block-triangular operator on the Lanczos spaces of lambda
  * and psi (exact when the spaces are invariant).  The forward states are kept
- * every ceil(sqrt(nsteps)) steps and recomputed segment by segment.
+ * every ceil(sqrt(nsteps)) steps and recomputed segment by segment; for sums of
+ * site terms up to 2^14 rows with one driven term the forward pass keeps its
+ * projections instead, if they take at most 2 GiB, and nothing is recomputed.
  * psi0_dev, target_dev: complex128[n] device buffers (read only).  Writes
  * *F_out and dFdu_out[0..K-1] (host) and synchronises hip_stream.  Device
- * workspace O((sqrt(nsteps) s + 2 m) n), allocated for the call.  Needs the
+ * workspace O((sqrt(nsteps) s + 2 m) n) -- with kept projections up to 16 GiB,
+ * at most half of the free memory --, allocated for the call.  Needs the
  * CSR operator: kept for n <= 2^22, above that only with CFET_KEEP_CSR at
  * create (CFET_EUNSUPPORTED otherwise). */
 CFET_API int cfet_gradient(cfet_ctx *c, const void *psi0_dev, const void *target_dev, double t0,

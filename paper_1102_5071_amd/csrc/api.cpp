@@ -107,6 +107,10 @@ int64_t coop_grid_blocks(int64_t n, int cus) {
 
 // device bytes the gradient may spend on keeping the recomputed projections
 constexpr size_t kGradStoreMax = size_t(16) << 30;
+// ... and on keeping those of the whole forward pass, and the lambda bases of
+// the exponentials whose Frechet terms are taken together (cfet_gradient)
+constexpr size_t kGradWholeMax = size_t(2) << 30;
+constexpr size_t kGradBasisMax = size_t(256) << 20;
 static_assert(sizeof(cfet_dt_choice) == 96 && offsetof(cfet_dt_choice, rounds) == 92,
               "cfet_dt_choice layout is part of the ABI");
 static_assert(sizeof(cfet_stats_t) == 120 && offsetof(cfet_stats_t, matrix_bytes) == 112,
@@ -521,6 +525,41 @@ hipError_t persistent_exponential(cfet_ctx* c, int path, double2* psi, double2* 
                  : cfet::launch_persistent(pa, path == 2 ? c->preset_single : c->preset_coop,
                                            path == 2, path == 3 ? c->coop_blocks : 1, st,
                                            bar == nullptr);
+  if (timed && e == hipSuccess) {
+    (void)hipEventRecord(c->events.end[c->events.used], st);
+    c->events.used += 1;
+  }
+  return e;
+}
+
+// The backward exponentials exp(+i dt H) of nsteps steps of s, from the last to
+// the first, in one launch on the site-operator form: lambda in place, the basis
+// and projection of each kept (application order of the forward pass, whose
+// weight table wts is).
+hipError_t site_backward(cfet_ctx* c, double2* lam, double2* basis, LzScalars* X,
+                         const double* wts, double dt, int64_t nsteps, int s, int m,
+                         hipStream_t st) {
+  cfet::PersistArgs pa{};
+  pa.real_vals = c->real_vals ? 1 : 0;
+  pa.n = c->n;
+  pa.nterms = c->nterms;
+  pa.wts = wts;
+  pa.s = s;
+  pa.nsteps = nsteps;
+  pa.m = m;
+  pa.dt = -dt;
+  pa.psi = lam;
+  pa.basis = basis;
+  pa.zbuf = c->zbuf;
+  pa.stats = c->stats;
+  pa.spin_limit = c->spin_limit;
+  pa.export_T = X;
+  pa.export_each = 1;
+  pa.rev = 1;
+  pa.basis_each = 1;
+  const bool timed = c->profiling && c->events.used < c->events.cap;
+  if (timed) (void)hipEventRecord(c->events.begin[c->events.used], st);
+  const hipError_t e = cfet::launch_site(c->site, pa, st);
   if (timed && e == hipSuccess) {
     (void)hipEventRecord(c->events.end[c->events.used], st);
     c->events.used += 1;
@@ -2096,9 +2135,11 @@ int run_cheb(cfet_ctx* c, double t0, double dt, int64_t nsteps, const SchemeTabl
 
 // cfet_propagate on psi_dev in the stored row order (user_order false: the
 // gradient's own buffers) or in the caller's order (permuted in and out when
-// the CSR paths run on a row order of their own).
+// the CSR paths run on a row order of their own).  export_T, export_Y: the
+// projection and H_1 w_j of every exponential (persistent paths only).
 int propagate_impl(cfet_ctx* c, void* psi_dev, double t0, double dt, int64_t nsteps,
-                   int32_t scheme, int32_t krylov_m, void* hip_stream, bool user_order) {
+                   int32_t scheme, int32_t krylov_m, void* hip_stream, bool user_order,
+                   LzScalars* export_T = nullptr, double2* export_Y = nullptr) {
   if (!c) return fail(nullptr, CFET_EINVAL, "null context");
   if (!psi_dev) return fail(c, CFET_EINVAL, "null psi");
   if (nsteps < 0) return fail(c, CFET_EINVAL, "nsteps < 0");
@@ -2137,7 +2178,8 @@ int propagate_impl(cfet_ctx* c, void* psi_dev, double t0, double dt, int64_t nst
     return ep == hipSuccess ? CFET_OK : hip_fail(c, ep, "permute psi out");
   };
   if (path != 1) {
-    const int rp = propagate_persistent(c, psi_dev, t0, dt, nsteps, sc, m, path, st);
+    const int rp = propagate_persistent(c, psi_dev, t0, dt, nsteps, sc, m, path, st, nullptr,
+                                        export_T, export_Y);
     return rp == CFET_OK ? permute_out() : rp;
   }
   c->h_W[0] = static_cast<double2*>(psi_dev);
@@ -2327,8 +2369,7 @@ int cfet_gradient(cfet_ctx* c, const void* psi0_dev, const void* target_dev, dou
   } swap_guard(c, dmod);
 
   const int64_t N = nsteps;
-  const int64_t seg = (N > 0) ? std::max<int64_t>(1, int64_t(std::ceil(std::sqrt(double(N))))) : 1;
-  const int64_t nseg = (N + seg - 1) / seg;
+  int64_t seg = (N > 0) ? std::max<int64_t>(1, int64_t(std::ceil(std::sqrt(double(N))))) : 1;
   GradBuffers gb;
   double2 *psi = nullptr, *lam = nullptr, *vpsi = nullptr, *vlam = nullptr, *ckpt = nullptr,
           *before = nullptr, *cpart = nullptr, *cmat = nullptr, *dz = nullptr, *zval = nullptr,
@@ -2343,31 +2384,62 @@ int cfet_gradient(cfet_ctx* c, const void* psi0_dev, const void* target_dev, dou
   // the backward sweep then runs no Lanczos recurrence from psi.  That store
   // takes seg * s * m vectors; above kGradStoreMax (or half the free device
   // memory) the recurrence from psi is rerun instead, with the same result.
+  //
+  // On the site-operator form the whole pass is one segment while its store
+  // stays within kGradWholeMax (and a quarter of the free memory): the forward
+  // pass keeps it and nothing is recomputed.  The backward exponentials then
+  // run many to a launch, each keeping its lambda basis, and their Frechet terms
+  // are taken together, exponentials side by side.  (2^14 rows, 40 steps of 5
+  // exponentials with 20 vectors: 46.7 ms with the recomputation and one
+  // exponential, its Frechet term after it, at a time; 24.7 ms this way, 1.2 ms
+  // of them in the Frechet kernels.  The call allocates its store, so it is kept
+  // to 2 GiB; the 256 MiB of lambda bases hold 50 exponentials there.)
   const int rpath = choose_path_csr(c);
+  const bool sited = rpath != 1 && c->site.ok && c->nterms == 1;
+  const size_t step_bytes = size_t(sc.s) * size_t(m) * nn * sizeof(double2);
+  if (sited && N > 0 && N <= 16384 / sc.s && size_t(N) <= kGradWholeMax / step_bytes) {
+    size_t free_b = 0, total_b = 0;
+    if (hipMemGetInfo(&free_b, &total_b) == hipSuccess && size_t(N) * step_bytes <= free_b / 4)
+      seg = N;
+  }
+  const int64_t nseg = (N + seg - 1) / seg;
   const size_t ystore = size_t(seg) * size_t(sc.s) * size_t(m) * nn * sizeof(double2);
   bool keep = rpath != 1 && c->nterms == 1 && ystore <= kGradStoreMax;
   if (keep) {
     size_t free_b = 0, total_b = 0;
     keep = hipMemGetInfo(&free_b, &total_b) == hipSuccess && ystore <= free_b / 2;
   }
-  double2* Yall = nullptr;
+  const bool batched = sited && keep;
+  const bool whole = batched && nseg == 1;
+  // steps whose backward exponentials share a launch, and their exponentials
+  const int64_t bsteps = std::max<int64_t>(
+      1, std::min<int64_t>({seg, int64_t(kGradBasisMax / step_bytes), 4096 / sc.s}));
+  const size_t bexp = size_t(bsteps) * size_t(sc.s);
+  double2 *Yall = nullptr, *gval = nullptr;
   LzScalars* Tall = nullptr;
   hipError_t e = gb.get(&psi, nn);
   if (e == hipSuccess) e = gb.get(&lam, nn);
   if (e == hipSuccess) e = gb.get(&vpsi, size_t(std::max(m - 1, 1)) * nn);
-  if (e == hipSuccess) e = gb.get(&vlam, size_t(std::max(m - 1, 1)) * nn);
+  if (e == hipSuccess) e = gb.get(&vlam, batched ? bexp * size_t(m) * nn : size_t(std::max(m - 1, 1)) * nn);
   if (e == hipSuccess) e = gb.get(&ckpt, size_t(std::max<int64_t>(nseg, 1)) * nn);
   if (e == hipSuccess && !keep) e = gb.get(&before, size_t(seg) * size_t(sc.s) * nn);
   if (e == hipSuccess && keep) e = gb.get(&Yall, size_t(seg) * size_t(sc.s) * size_t(m) * nn);
   if (e == hipSuccess && keep) e = gb.get(&Tall, size_t(seg) * size_t(sc.s));
-  if (e == hipSuccess)
+  if (e == hipSuccess && batched) {
+    size_t blocks = 0;  // the last launch of a segment may hold fewer steps
+    for (int64_t q = 1; q <= bsteps; ++q)
+      blocks = std::max(blocks, size_t(q) * sc.s * cfet::frechet_batch_blocks(n, int(q) * sc.s));
+    e = gb.get(&cpart, blocks * size_t(m) * size_t(m));
+    if (e == hipSuccess) e = gb.get(&gval, bexp);
+  } else if (e == hipSuccess) {
     e = gb.get(&cpart, size_t(cfet::frechet_part_blocks(n)) * cfet::kMaxM * cfet::kMaxM);
-  if (e == hipSuccess) e = gb.get(&cmat, size_t(cfet::kMaxM) * cfet::kMaxM);
+  }
+  if (e == hipSuccess) e = gb.get(&cmat, (batched ? bexp : 1) * size_t(cfet::kMaxM) * cfet::kMaxM);
   if (e == hipSuccess) e = gb.get(&dz, size_t(K));
   if (e == hipSuccess) e = gb.get(&zval, 1);
   if (e == hipSuccess) e = gb.get(&zpart, size_t(cfet::zdot_blocks(n)));
   if (e == hipSuccess) e = gb.get(&Spsi, 1);
-  if (e == hipSuccess) e = gb.get(&Slam, 1);
+  if (e == hipSuccess) e = gb.get(&Slam, batched ? bexp : 1);
   if (e != hipSuccess) return hip_fail(c, e, "cfet_gradient: workspace");
   const size_t vb = nn * sizeof(double2);
   // ---- forward pass, keeping psi at the start of every segment
@@ -2375,10 +2447,12 @@ int cfet_gradient(cfet_ctx* c, const void* psi0_dev, const void* target_dev, dou
   e = c->perm ? cfet::launch_permute(psi, static_cast<const double2*>(psi0_dev), c->perm, n, st)
               : hipMemcpyAsync(psi, psi0_dev, vb, hipMemcpyDeviceToDevice, st);
   for (int64_t sg = 0; sg < nseg && e == hipSuccess; ++sg) {
-    e = hipMemcpyAsync(ckpt + size_t(sg) * nn, psi, vb, hipMemcpyDeviceToDevice, st);
+    if (!whole)
+      e = hipMemcpyAsync(ckpt + size_t(sg) * nn, psi, vb, hipMemcpyDeviceToDevice, st);
     if (e != hipSuccess) break;
     const int64_t s0 = sg * seg, len = std::min(seg, N - s0);
-    rc = propagate_impl(c, psi, t0 + double(s0) * dt, dt, len, scheme, m, st, false);
+    rc = propagate_impl(c, psi, t0 + double(s0) * dt, dt, len, scheme, m, st, false,
+                        whole ? Tall : nullptr, whole ? Yall : nullptr);
     if (rc != CFET_OK) return rc;
   }
   if (e == hipSuccess)
@@ -2518,9 +2592,11 @@ int cfet_gradient(cfet_ctx* c, const void* psi0_dev, const void* target_dev, dou
 
   for (int64_t sg = nseg - 1; sg >= 0 && e == hipSuccess; --sg) {
     const int64_t s0 = sg * seg, s1 = std::min(N, s0 + seg);
-    e = hipMemcpyAsync(psi, ckpt + size_t(sg) * nn, vb, hipMemcpyDeviceToDevice, st);
+    if (!whole) e = hipMemcpyAsync(psi, ckpt + size_t(sg) * nn, vb, hipMemcpyDeviceToDevice, st);
     Wf[0] = psi;
-    if (e == hipSuccess && rpath != 1) {
+    if (whole) {
+      // kept by the forward pass, whose weight table is still in place
+    } else if (e == hipSuccess && rpath != 1) {
       rc = propagate_persistent(c, psi, t0 + double(s0) * dt, dt, s1 - s0, sc, m, rpath, st,
                                 before, Tall, Yall);
       if (rc != CFET_OK) return rc;
@@ -2567,7 +2643,17 @@ int cfet_gradient(cfet_ctx* c, const void* psi0_dev, const void* target_dev, dou
     if (e == hipSuccess) e = hipMemcpyAsync(d_cursor, hcur, sizeof(int), hipMemcpyHostToDevice, st);
     if (e == hipSuccess) e = hipEventRecord(staged, st);
     if (e == hipSuccess) staged_pending = true;
-    for (size_t x = idx; x-- > 0 && e == hipSuccess;) e = enqueue_back(st, x);
+    for (size_t x = idx; x-- > 0 && e == hipSuccess && !batched;) e = enqueue_back(st, x);
+    for (int64_t q1 = s1 - s0; q1 > 0 && e == hipSuccess && batched; q1 -= bsteps) {
+      const int64_t q0 = std::max<int64_t>(0, q1 - bsteps);
+      const size_t ix = size_t(q0) * sc.s;
+      e = site_backward(c, lam, vlam, Slam, c->d_wts + ix * (c->nterms + 1), dt, q1 - q0, sc.s, m,
+                        st);
+      if (e == hipSuccess)
+        e = cfet::launch_frechet_batch(n, m, int(q1 - q0) * sc.s, vlam, Yall + ix * size_t(m) * nn,
+                                       Tall + ix, Slam, cpart, cmat, gval, dt, d_recs + ix, dz, K,
+                                       c->stats, st);
+    }
   }
   if (e != hipSuccess) return hip_fail(c, e, "cfet_gradient: backward sweep");
   std::vector<double2> hz(size_t(K) + 1);

@@ -284,6 +284,15 @@ int frechet_part_blocks(int64_t n);  // blocks of partials either C kernel write
 hipError_t launch_frechet_dots(int64_t n, const double2* lam0, const double2* lam_rest,
                                const double2* Y, const LzScalars* Spsi, const LzScalars* Slam,
                                double2* part, double2* C, hipStream_t st);
+// The Frechet terms of E exponentials at once: their projections and lambda
+// bases and Y at consecutive records (Spsi, Slam, rec) and every m * n elements
+// (lam, Y), in part (frechet_batch_blocks(n, E) * m * m per exponential), C
+// (kMaxM^2 per exponential) and g (one per exponential) as workspaces.
+int frechet_batch_blocks(int64_t n, int E);
+hipError_t launch_frechet_batch(int64_t n, int m, int E, const double2* lam, const double2* Y,
+                                const LzScalars* Spsi, const LzScalars* Slam, double2* part,
+                                double2* C, double2* g, double dt, const GradRec* rec,
+                                double2* dz, int K, DevStats* stats, hipStream_t st);
 hipError_t launch_frechet_c(const DevCSR& A, int term, const double2* psi0,
                             const double2* psi_rest, const double2* lam0, const double2* lam_rest,
                             const LzScalars* Spsi, const LzScalars* Slam, double2* part,
@@ -335,6 +344,10 @@ struct PersistArgs {
   int export_each;          // 1: export_T / export_Y hold one record per exponential of
                             // the call (application order e: export_T + e,
                             // export_Y + e*m*n) instead of the last one only
+  int rev;                  // site-operator form only: 1 takes the call's exponentials (and
+                            // their weights and records) from the last to the first
+  int basis_each;           // site-operator form only: 1 keeps the basis of every
+                            // exponential e, its vector j >= 0 at basis + (e*m + j)*n
   int real_vals;            // 1: every imaginary part of val is 0 (real-valued kernels)
 };
 

@@ -105,10 +105,19 @@ __global__ __launch_bounds__(kCBlock) void k_frechet_c(
 // rows in tiles of kDRows staged in LDS.
 constexpr int kDRows = 32;
 
+// blockIdx.y: exponential of a batch (vectors `stride` elements, partials
+// `pstride` apart).
 __global__ __launch_bounds__(kCBlock) void k_frechet_dots(
     int64_t n, const double2* __restrict__ lam0, const double2* __restrict__ lam_rest,
     const double2* __restrict__ Y, const LzScalars* __restrict__ Spsi,
-    const LzScalars* __restrict__ Slam, double2* __restrict__ part) {
+    const LzScalars* __restrict__ Slam, double2* __restrict__ part, int64_t stride,
+    int64_t pstride) {
+  lam0 += blockIdx.y * stride;
+  lam_rest += blockIdx.y * stride;
+  Y += blockIdx.y * stride;
+  Spsi += blockIdx.y;
+  Slam += blockIdx.y;
+  part += blockIdx.y * pstride;
   __shared__ double2 Ys[kDRows][kMaxM];
   __shared__ double2 Us[kDRows][kMaxM];
   const int mp = Spsi->m_eff, ml = Slam->m_eff;
@@ -160,11 +169,17 @@ __global__ __launch_bounds__(kCBlock) void k_frechet_dots(
 
 // C[k][j] = inv_lam[k] inv_psi[j] * sum over blocks of the partials, one
 // wavefront per pair: lane l adds blocks l, l + 64, ... in order, then a fixed
-// butterfly over the lanes (the same order on every run).
+// butterfly over the lanes (the same order on every run).  blockIdx.y: exponential
+// of a batch.
 __global__ __launch_bounds__(256) void k_frechet_c_reduce(const double2* __restrict__ part,
                                                           int nb, const LzScalars* Spsi,
                                                           const LzScalars* Slam,
-                                                          double2* __restrict__ C) {
+                                                          double2* __restrict__ C,
+                                                          int64_t pstride) {
+  part += blockIdx.y * pstride;
+  Spsi += blockIdx.y;
+  Slam += blockIdx.y;
+  C += (int64_t)blockIdx.y * kMaxM * kMaxM;
   const int mp = Spsi->m_eff, ml = Slam->m_eff;
   const int npairs = ml * mp;
   const int pair = blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6);
@@ -195,16 +210,22 @@ __global__ __launch_bounds__(256) void k_frechet_c_reduce(const double2* __restr
 __global__ __launch_bounds__(kSmallThreads) void k_frechet_small(
     const LzScalars* __restrict__ Spsi, const LzScalars* __restrict__ Slam,
     const double2* __restrict__ C, double dt, double2* __restrict__ dz, DevStats* stats,
-    const GradRec* __restrict__ rec, int* cursor) {
+    const GradRec* __restrict__ rec, int* cursor, double2* __restrict__ gout) {
   __shared__ double2 tb[2][2 * kMaxM];
   __shared__ double red[2];
+  Spsi += blockIdx.x;
+  Slam += blockIdx.x;
+  C += (int64_t)blockIdx.x * kMaxM * kMaxM;
   const int ml = Slam->m_eff, mp = Spsi->m_eff;
   const int nm = ml + mp;
   const int r = threadIdx.x;
   // the record of this exponential was taken by the prologue: step the cursor
   // to the one before it (also for a zero state)
   if (cursor && r == 0) *cursor -= 1;
-  if (ml == 0 || mp == 0) return;  // a zero state: no contribution
+  if (ml == 0 || mp == 0) {  // a zero state: no contribution
+    if (gout && r == 0) gout[blockIdx.x] = make_double2(0.0, 0.0);
+    return;
+  }
   // row r of C in registers when mp <= kSmallC (the Taylor loop then reads
   // only the term vector from LDS)
   const bool reg_c = mp <= kSmallC;
@@ -305,10 +326,14 @@ __global__ __launch_bounds__(kSmallThreads) void k_frechet_small(
     const double bb = Slam->beta0 * Spsi->beta0;
     const double2 g = make_double2(bb * vr.x, bb * vr.y);
     // (piece, weight) pairs of this exponential from its record
-    const int npairs = rec->np;
-    for (int q = 0; q < npairs; ++q) {
-      dz[rec->p[q]].x += rec->w[q] * g.x;
-      dz[rec->p[q]].y += rec->w[q] * g.y;
+    if (gout) {
+      gout[blockIdx.x] = g;
+    } else {
+      const int npairs = rec->np;
+      for (int q = 0; q < npairs; ++q) {
+        dz[rec->p[q]].x += rec->w[q] * g.x;
+        dz[rec->p[q]].y += rec->w[q] * g.y;
+      }
     }
     if (!(isfinite(g.x) && isfinite(g.y)) && stats->status == CFET_OK)
       stats->status = CFET_ENONFINITE;
@@ -336,13 +361,19 @@ __device__ __forceinline__ double lane_above(double v) {  // lane r receives lan
 __global__ __launch_bounds__(64) void k_frechet_small_wave(
     const LzScalars* __restrict__ Spsi, const LzScalars* __restrict__ Slam,
     const double2* __restrict__ C, double dt, double2* __restrict__ dz, DevStats* stats,
-    const GradRec* __restrict__ rec, int* cursor) {
+    const GradRec* __restrict__ rec, int* cursor, double2* __restrict__ gout) {
   __shared__ double2 tw[64];
+  Spsi += blockIdx.x;
+  Slam += blockIdx.x;
+  C += (int64_t)blockIdx.x * kMaxM * kMaxM;
   const int ml = Slam->m_eff, mp = Spsi->m_eff;
   const int nm = ml + mp;
   const int r = threadIdx.x;
   if (cursor && r == 0) *cursor -= 1;
-  if (ml == 0 || mp == 0) return;  // a zero state: no contribution
+  if (ml == 0 || mp == 0) {  // a zero state: no contribution
+    if (gout && r == 0) gout[blockIdx.x] = make_double2(0.0, 0.0);
+    return;
+  }
   double2 creg[kSmallC];
 #pragma unroll
   for (int j = 0; j < kSmallC; ++j)
@@ -417,13 +448,51 @@ __global__ __launch_bounds__(64) void k_frechet_small_wave(
   if (r == 0) {
     const double bb = Slam->beta0 * Spsi->beta0;
     const double2 g = make_double2(bb * vr.x, bb * vr.y);
-    const int npairs = rec->np;
-    for (int q = 0; q < npairs; ++q) {
-      dz[rec->p[q]].x += rec->w[q] * g.x;
-      dz[rec->p[q]].y += rec->w[q] * g.y;
+    if (gout) {
+      gout[blockIdx.x] = g;
+    } else {
+      const int npairs = rec->np;
+      for (int q = 0; q < npairs; ++q) {
+        dz[rec->p[q]].x += rec->w[q] * g.x;
+        dz[rec->p[q]].y += rec->w[q] * g.y;
+      }
     }
     if (!(isfinite(g.x) && isfinite(g.y)) && stats->status == CFET_OK)
       stats->status = CFET_ENONFINITE;
+  }
+}
+
+// dz[p] += w g over a batch's exponentials from the last to the first (the order
+// in which they are taken one at a time); thread p owns piece p.
+constexpr int kAccumE = 256;
+__global__ __launch_bounds__(256) void k_frechet_accum(const GradRec* __restrict__ rec,
+                                                       const double2* __restrict__ g, int E,
+                                                       double2* __restrict__ dz, int K) {
+  __shared__ double2 gs[kAccumE];
+  __shared__ double ws[kAccumE][4];
+  __shared__ int ps[kAccumE][4];
+  for (int e1 = E; e1 > 0; e1 -= kAccumE) {
+    const int e0 = max(0, e1 - kAccumE);
+    __syncthreads();
+    for (int e = e0 + threadIdx.x; e < e1; e += blockDim.x) {
+      gs[e - e0] = g[e];
+      for (int q = 0; q < 4; ++q) {
+        const bool used = q < rec[e].np;
+        ps[e - e0][q] = used ? rec[e].p[q] : -1;
+        ws[e - e0][q] = used ? rec[e].w[q] : 0.0;
+      }
+    }
+    __syncthreads();
+    for (int p = threadIdx.x; p < K; p += blockDim.x) {
+      double2 a = dz[p];
+      for (int e = e1 - e0 - 1; e >= 0; --e)
+        for (int q = 0; q < 4; ++q)
+          if (ps[e][q] == p) {
+            a.x += ws[e][q] * gs[e].x;
+            a.y += ws[e][q] * gs[e].y;
+          }
+      dz[p] = a;
+    }
   }
 }
 
@@ -514,7 +583,7 @@ static hipError_t launch_c_reduce(const double2* part, int nb, const LzScalars* 
                                   const LzScalars* Slam, double2* C, hipStream_t st) {
   // one wavefront per pair in use (at most kMaxM^2; the kernel reads m_eff)
   hipLaunchKernelGGL(k_frechet_c_reduce, dim3((kMaxM * kMaxM + 3) / 4), dim3(256), 0, st, part,
-                     nb, Spsi, Slam, C);
+                     nb, Spsi, Slam, C, int64_t(0));
   return hipGetLastError();
 }
 
@@ -523,7 +592,7 @@ hipError_t launch_frechet_dots(int64_t n, const double2* lam0, const double2* la
                                double2* part, double2* C, hipStream_t st) {
   const int nb = frechet_dots_blocks(n);
   hipLaunchKernelGGL(k_frechet_dots, dim3(nb), dim3(kCBlock), 0, st, n, lam0, lam_rest, Y, Spsi,
-                     Slam, part);
+                     Slam, part, int64_t(0), int64_t(0));
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   return launch_c_reduce(part, nb, Spsi, Slam, C, st);
@@ -541,17 +610,53 @@ hipError_t launch_frechet_c(const DevCSR& A, int term, const double2* psi0,
   return launch_c_reduce(part, nb, Spsi, Slam, C, st);
 }
 
+static bool small_wave(int mmax) { return mmax >= 1 && mmax <= kSmallC && 2 * mmax <= 64; }
+
+// Enough blocks over the batch to fill the chip; each exponential keeps a few
+// row ranges, so that its partials stay small.
+int frechet_batch_blocks(int64_t n, int E) {
+  const int64_t tiles = (n + kDRows - 1) / kDRows;
+  const int64_t want = (2048 + E - 1) / E;
+  return (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(tiles, 256), want));
+}
+
+hipError_t launch_frechet_batch(int64_t n, int m, int E, const double2* lam, const double2* Y,
+                                const LzScalars* Spsi, const LzScalars* Slam, double2* part,
+                                double2* C, double2* g, double dt, const GradRec* rec,
+                                double2* dz, int K, DevStats* stats, hipStream_t st) {
+  const int nb = frechet_batch_blocks(n, E);
+  const int64_t pstride = int64_t(nb) * m * m;
+  hipLaunchKernelGGL(k_frechet_dots, dim3(nb, E), dim3(kCBlock), 0, st, n, lam, lam + n, Y, Spsi,
+                     Slam, part, int64_t(m) * n, pstride);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_frechet_c_reduce, dim3((m * m + 3) / 4, E), dim3(256), 0, st, part, nb,
+                     Spsi, Slam, C, pstride);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  if (small_wave(m))
+    hipLaunchKernelGGL(k_frechet_small_wave, dim3(E), dim3(64), 0, st, Spsi, Slam, C, dt, dz,
+                       stats, rec, static_cast<int*>(nullptr), g);
+  else
+    hipLaunchKernelGGL(k_frechet_small, dim3(E), dim3(kSmallThreads), 0, st, Spsi, Slam, C, dt,
+                       dz, stats, rec, static_cast<int*>(nullptr), g);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_frechet_accum, dim3(1), dim3(256), 0, st, rec, g, E, dz, K);
+  return hipGetLastError();
+}
+
 hipError_t launch_frechet_small_rec(const LzScalars* Spsi, const LzScalars* Slam,
                                     const double2* C, double dt, const GradRec* cur,
                                     double2* dz, DevStats* stats, int* cursor, int mmax,
                                     hipStream_t st) {
   if (!cur) return hipErrorInvalidValue;
-  if (mmax >= 1 && mmax <= kSmallC && 2 * mmax <= 64) {
+  if (small_wave(mmax)) {
     hipLaunchKernelGGL(k_frechet_small_wave, dim3(1), dim3(64), 0, st, Spsi, Slam, C, dt, dz,
-                       stats, cur, cursor);
+                       stats, cur, cursor, static_cast<double2*>(nullptr));
   } else {
     hipLaunchKernelGGL(k_frechet_small, dim3(1), dim3(kSmallThreads), 0, st, Spsi, Slam, C, dt,
-                       dz, stats, cur, cursor);
+                       dz, stats, cur, cursor, static_cast<double2*>(nullptr));
   }
   return hipGetLastError();
 }

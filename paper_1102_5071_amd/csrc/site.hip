@@ -251,9 +251,6 @@ __device__ __forceinline__ void site_run(const SiteArgs& A, int rank, double2* x
   const int NB = A.blocks;
   const int nt1 = A.p.nterms + 1;
   double2* const psi = A.p.psi;
-  auto Uv = [&](int k) -> double2* {
-    return k == 0 ? psi : A.p.basis + (size_t)(k - 1) * (size_t)n;
-  };
   uint32_t qb = (uint32_t)(uintptr_t)(lds_cptr)xt + ((uint32_t)t << 4);
   asm volatile("" : "+v"(qb));
 
@@ -336,8 +333,11 @@ __device__ __forceinline__ void site_run(const SiteArgs& A, int rank, double2* x
   SiteTimer tm;
   tm.start(A.p.timing != 0 && rank == 0 && t == 0);
   bool ok = true;
-  for (int64_t step = 0; ok && step < A.p.nsteps; ++step) {
-    for (int i = A.p.s - 1; ok && i >= 0; --i) {
+  for (int64_t sq = 0; ok && sq < A.p.nsteps; ++sq) {
+    const int64_t step = A.p.rev ? A.p.nsteps - 1 - sq : sq;
+    for (int iq = 0; ok && iq < A.p.s; ++iq) {
+      const int i = A.p.rev ? iq : A.p.s - 1 - iq;
+      const int64_t eidx = step * A.p.s + (A.p.s - 1 - i);
       const double* const wts = A.p.wts + ((size_t)step * A.p.s + i) * nt1;
       // the sets' weights and the diagonal's
       const double ws0 = WTD ? 1.0 : wts[A.set_term[0]];
@@ -374,22 +374,30 @@ __device__ __forceinline__ void site_run(const SiteArgs& A, int rank, double2* x
       }
       const int m = A.p.m;
       int meff = m;
+      // where u_1 is kept; the later ones follow
+      auto first = [&]() -> double2* {
+        return A.p.basis + (A.p.basis_each ? ((size_t)eidx * m + 1) * n : 0);
+      };
+      double2* uk = first() + row0;
       bool zero = false;
       double scale = 0.0, alpha_prev = 0.0, inv_prev = 0.0;
       double S1 = 0.0, S2 = 0.0;
-      const int64_t eidx = step * A.p.s + (A.p.s - 1 - i);
       LzScalars* const XT =
           (A.p.export_T && A.p.export_each) ? A.p.export_T + eidx : A.p.export_T;
       double2* const XY = (A.p.export_Y && A.p.export_each)
                               ? A.p.export_Y + (size_t)eidx * (size_t)m * (size_t)n
                               : A.p.export_Y;
+      if (A.p.basis_each && act) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) (uk - n)[r * T] = u1[r];
+      }
       if (A.p.save && act) {
 #pragma unroll
         for (int r = 0; r < R; ++r) A.p.save[eidx * n + row0 + (uint32_t)(r * T)] = u1[r];
       }
       if (TEAM) {
         // u_0 = psi of the other blocks, once all have written it
-        if (eidx > 0 && !A.p.no_combine) {
+        if (sq + iq > 0 && !A.p.no_combine) {
           double v;
           if (!rec_wait(rec_u, lane < NB, lane, tag_u, A.p.spin_limit, v)) sh.bad = 1;
         }
@@ -503,9 +511,9 @@ __device__ __forceinline__ void site_run(const SiteArgs& A, int rank, double2* x
           record();
           if (stop) break;
           if (act) {
-            double2* const uk = Uv(k);
 #pragma unroll
-            for (int r = 0; r < R; ++r) uk[row0 + (uint32_t)(r * T)] = uc[r];
+            for (int r = 0; r < R; ++r) uk[r * T] = uc[r];
+            uk += n;
           }
         }
         if constexpr (TEAM) {
@@ -638,11 +646,13 @@ __device__ __forceinline__ void site_run(const SiteArgs& A, int rank, double2* x
         double2 sum[R];
 #pragma unroll
         for (int r = 0; r < R; ++r) sum[r] = make_double2(0.0, 0.0);
+        const double2* const uf = first();
         for (int k = 0; k < meff; k += Q) {
           double2 v[Q][R];
 #pragma unroll
           for (int q = 0; q < Q; ++q) {
-            const double2* const b = Uv(k + q < meff ? k + q : meff - 1);
+            const int kq = k + q < meff ? k + q : meff - 1;
+            const double2* const b = kq == 0 ? psi : uf + (size_t)(kq - 1) * (size_t)n;
 #pragma unroll
             for (int r = 0; r < R; ++r) v[q][r] = b[row0 + (uint32_t)(r * T)];
           }

@@ -134,6 +134,28 @@ def test_gradient_matches_oracle(model, L):
     assert np.max(np.abs(gg - g)) <= 1e-8 * np.max(np.abs(g))
 
 
+@pytest.mark.parametrize("L,N,scheme,m", [
+    (6, 40, "CF4:2", 40),         # the whole pass kept, more than one wavefront of scalars
+    (12, 45, "CF6:5Opt", 20),     # kept, the backward exponentials in two launches
+    (14, 27, "CF6:5Opt", 64),     # recomputed by segments of two launches, the last shorter
+    (9, 3, "CF8:11", 1),          # one vector per basis
+])
+def test_gradient_batches_match_one_exponential_at_a_time(L, N, scheme, m):
+    H0, Hk, _, psi0 = chain("ising", L, L)
+    rng = np.random.default_rng(L)
+    u, dt = rng.uniform(-1, 1, 4), 0.01 if m > 1 else 1e-4
+    drives = [{"kind": "pwc", "t_edges": np.linspace(0.0, N * dt, 5), "u": u}]
+    target = I.random_state(1 << L, rng)
+    got = []
+    for path in (None, "multi"):
+        with B.Propagator(H0, Hk, drives, path=path) as P:
+            got.append(P.gradient(dev(psi0), dev(target), 0.0, dt, N, scheme, m))
+            assert P.stats()["status"] == 0
+    (F, g), (Fo, go) = got
+    assert abs(F - Fo) <= 1e-10 * max(Fo, 1e-3)
+    assert np.max(np.abs(g - go)) <= 1e-8 * np.max(np.abs(go))
+
+
 def test_two_streams_and_two_contexts():
     # two contexts in flight on two streams, teams of 16 and 8 blocks
     jobs = []
