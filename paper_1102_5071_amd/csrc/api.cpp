@@ -2099,7 +2099,13 @@ int run_cheb(cfet_ctx* c, double t0, double dt, int64_t nsteps, const SchemeTabl
         const bool ev = timed && c->events.used < c->events.cap;
         const double scale = (k == 1 ? 1.0 : 2.0) / h;
         if (ev) (void)hipEventRecord(c->events.begin[c->events.used], st);
-        const cfet::ChebTerm ct{prev, psi, scale, sigma, coef(k), k == 1 ? 1 : 0};
+        cfet::ChebTerm ct{prev, psi, scale, sigma, coef(k), k == 1 ? 1 : 0, 0, {}, {}};
+        if (c->parity.ok && (k % 3 == 0 || k == K)) {
+          // the terms since the last multiple of three
+          ct.acc = 1;
+          ct.cx = k % 3 != 1 ? coef(k - 1) : make_double2(0.0, 0.0);
+          ct.cp = k % 3 == 0 ? coef(k - 2) : make_double2(0.0, 0.0);
+        }
         if (c->parity.ok) {
           // as on the split layout, the term is applied in the second sweep
           e = cfet::launch_parity_apply(c->parity, tw, cur, y, ct, st);

@@ -183,6 +183,10 @@ struct ChebTerm {
   double sigma;
   double2 ck;
   int first;
+  // site-operator form: psi takes several terms at once (acc 0: none at this
+  // one); cx and cp are the factors of x and of prev as it was
+  int acc;
+  double2 cx, cp;
 };
 // y = H x, then the Chebyshev term on the split layout (the first pass writes
 // y, the second applies the term instead of storing y).

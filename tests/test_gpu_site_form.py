@@ -216,6 +216,19 @@ def test_chebyshev_matches_oracle(L):
     assert st["status"] == 0 and rel(out, ref) <= 1e-10
 
 
+@pytest.mark.parametrize("dt", [0.0, 1e-13, 1e-7, 1e-5, 1e-4, 5e-4, 1e-3, 2e-3, 4e-3, 8e-3])
+def test_chebyshev_short_series(dt):
+    # psi takes three terms at a time: series of zero to a dozen terms
+    p = I.config_heisenberg(L=16)
+    with B.Propagator(p.H0, p.Hk, p.drives) as P:
+        psi = dev(p.psi0)
+        P.propagate_chebyshev(psi, 0.0, dt, 1, "CF4:2", 1e-12)
+        assert P.stats()["status"] == 0
+        out = psi.cpu().numpy()
+    ref = C.propagate_chebyshev(p.H0, p.Hk, p.drives, p.psi0, 0.0, dt, 1, "CF4:2", 1e-12)
+    assert rel(out, ref) <= 1e-12
+
+
 def test_static_and_streams_and_repeat():
     # the allocation-free entry point, another stream, and bit-equal repeats
     p = I.config_heisenberg(L=16)
