@@ -81,7 +81,7 @@ __device__ __forceinline__ RowMap row_map(const BGroup& gr, int g, int lb) {
 // one instance are contiguous, so its reduction reads them coalesced.
 template <int W>
 __device__ void block_partial(double v, const BGroup& gr, double* red, const BLaunch& L,
-                              int lb) {
+                              int local) {
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1)
     if (off >= gr.lpr) v += __shfl_xor(v, off, 64);
@@ -91,7 +91,7 @@ __device__ void block_partial(double v, const BGroup& gr, double* red, const BLa
   if (threadIdx.x < gr.B) {
     double t = 0.0;
     for (int i = 0; i < W; ++i) t += red[i * 64 + threadIdx.x];
-    L.part[(int64_t)(gr.slot0 + threadIdx.x) * L.pstride + (lb - gr.block0)] = t;
+    L.part[(int64_t)(gr.slot0 + threadIdx.x) * L.pstride + local] = t;
   }
 }
 
@@ -119,7 +119,7 @@ __global__ __launch_bounds__(64 * W) void k_b_norm(BLaunch L) {
       s += v.x * v.x + v.y * v.y;
     }
   }
-  block_partial<W>(s, gr, red, L, lb);
+  block_partial<W>(s, gr, red, L, lb - gr.block0);
 }
 
 // ---- y = H_w v_k (v_k = V_k * inv_k) and partials of Re<v_k, y>
@@ -205,7 +205,148 @@ __global__ __launch_bounds__(64 * W) void k_b_spmm(BLaunch L, int k) {
       s += (xo.x * yv.x + xo.y * yv.y) * invk;
     }
   }
-  block_partial<W>(s, gr, red, L, lb);
+  block_partial<W>(s, gr, red, L, lb - gr.block0);
+}
+
+// ---- the same in one or two sweeps over LDS tiles, for groups whose shared
+// operator is one driven term that flips single row bits with real factors and
+// whose H0 are real diagonals (a driven spin chain).
+//
+// The B = 2^b instances of a group are the low bits of a packed element's index,
+// so the group is one vector of 2^nv elements and a flip of row bit i one of
+// element bit i + b.  k_b_low holds 2^12 consecutive elements in LDS and takes
+// the flips below bit 12 and the diagonal; the flips above are left to k_b_high,
+// whose tiles hold the top bits (nv - 12 of them, with the 24 - nv lowest: whole
+// 128-byte lines up to nv = 21), or gathered when there are at most kFlipGather:
+// a sweep costs three vectors of traffic.  k_b_spmm reads every row's L
+// neighbours instead, most from other XCDs' lines, and 16-byte diagonals.  Both
+// are bound by the traffic beyond the L2s.  64 chains of 2^12 to 2^18 rows
+// (77 MB a vector): k_b_spmm 160 us, the two sweeps 32 + 48 us (4.8 TB/s and
+// 5.6 TB/s); the whole step 14.0 -> 10.2 ms for four of them.
+constexpr int kFlipT = 512;
+constexpr int kFlipR = (1 << kFlipBits) / kFlipT;
+
+template <bool HI>
+__device__ __forceinline__ int flip_group(const BGroup* G, int ng, int b) {
+  int lo = 0, hi = ng - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if ((HI ? G[mid].hblock0 : G[mid].sblock0) <= b) lo = mid;
+    else hi = mid - 1;
+  }
+  return lo;
+}
+
+__device__ __forceinline__ void flip_add(double2& a, double c, double2 x) {
+  a.x = fma(c, x.x, a.x);
+  a.y = fma(c, x.y, a.y);
+}
+
+// flips of the tile's top three bits: another register of the same thread
+__device__ __forceinline__ void flip_registers(double2 (&acc)[kFlipR], const double2 (&x)[kFlipR],
+                                               const double* c) {
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    const double cq = c[q];
+#pragma unroll
+    for (int r = 0; r < kFlipR; ++r) flip_add(acc[r], cq, x[r ^ (1 << q)]);
+  }
+}
+
+__global__ __launch_bounds__(kFlipT, 4) void k_b_high(BLaunch L, int k) {
+  __shared__ double2 xt[1 << kFlipBits];
+  const int g = flip_group<true>(L.groups, L.ngroups, blockIdx.x);
+  const BGroup gr = L.groups[g];
+  if (group_idle(gr, L.S.done)) return;
+  const int t = threadIdx.x;
+  const int low = 2 * kFlipBits - gr.nv;
+  const uint32_t tile = (uint32_t)(blockIdx.x - gr.hblock0) << low;
+  const double2* __restrict__ x = L.V + (int64_t)k * L.ntot + gr.voff;
+  double2* __restrict__ y = L.Y + gr.voff;
+  uint32_t idx[kFlipR];
+  double2 xo[kFlipR], acc[kFlipR];
+#pragma unroll
+  for (int r = 0; r < kFlipR; ++r) {
+    const uint32_t q = (uint32_t)(t + r * kFlipT);
+    idx[r] = (q & ((1u << low) - 1u)) | tile | ((q >> low) << kFlipBits);
+    xo[r] = x[idx[r]];
+    acc[r] = make_double2(0.0, 0.0);
+  }
+#pragma unroll
+  for (int r = 0; r < kFlipR; ++r) xt[t + r * kFlipT] = xo[r];
+  __syncthreads();
+  const double* __restrict__ c = gr.coef + kFlipBits - low;  // by tile bit
+  flip_registers(acc, xo, c + kFlipBits - 3);
+  for (int p = low; p < kFlipBits - 3; ++p) {
+    const double cp = c[p];
+#pragma unroll
+    for (int r = 0; r < kFlipR; ++r) flip_add(acc[r], cp, xt[(t ^ (1 << p)) + r * kFlipT]);
+  }
+#pragma unroll
+  for (int r = 0; r < kFlipR; ++r) y[idx[r]] = acc[r];
+}
+
+__global__ __launch_bounds__(kFlipT, 4) void k_b_low(BLaunch L, int k) {
+  __shared__ double2 xt[1 << kFlipBits];
+  const int g = flip_group<false>(L.groups, L.ngroups, blockIdx.x);
+  const BGroup gr = L.groups[g];
+  if (group_idle(gr, L.S.done)) return;
+  const int t = threadIdx.x;
+  const int tile = blockIdx.x - gr.sblock0;
+  const uint32_t e0 = (uint32_t)tile << kFlipBits;
+  const uint32_t ne = 1u << gr.nv;
+  const BState* st = L.st;
+  const int slot = gr.slot0 + (t & (gr.B - 1));
+  const bool act = L.S.done[slot] == 0;
+  const double* __restrict__ wt =
+      st->wts + ((int64_t)st->cursor * st->nslots + slot) * st->K1;
+  const double w0 = wt[0], w1 = wt[1];
+  const double invk = act ? L.S.inv[(int64_t)slot * kMaxM + k] : 0.0;
+  const double2* __restrict__ x = L.V + (int64_t)k * L.ntot + gr.voff;
+  double2* __restrict__ y = L.Y + gr.voff;
+  double2 xo[kFlipR], acc[kFlipR];
+  double d[kFlipR];
+#pragma unroll
+  for (int r = 0; r < kFlipR; ++r) {
+    const uint32_t i = e0 + (uint32_t)(t + r * kFlipT);
+    const bool in = act && i < ne;  // (lanes of an instance only read their own)
+    xo[r] = in ? x[i] : make_double2(0.0, 0.0);
+    acc[r] = (in && gr.hblocks) ? y[i] : make_double2(0.0, 0.0);
+    d[r] = in ? __builtin_nontemporal_load(gr.diagr + i) : 0.0;
+  }
+#pragma unroll
+  for (int r = 0; r < kFlipR; ++r) xt[t + r * kFlipT] = xo[r];
+  __syncthreads();
+  const double* __restrict__ c = gr.coef;
+  flip_registers(acc, xo, c + kFlipBits - 3);
+  if (!gr.hblocks)
+    for (int v = kFlipBits; v < gr.nv; ++v) {
+      const double cv = c[v];
+#pragma unroll
+      for (int r = 0; r < kFlipR; ++r)
+        if (act) flip_add(acc[r], cv, x[(e0 + (uint32_t)(t + r * kFlipT)) ^ (1u << v)]);
+    }
+  for (int p = 0; (1 << p) < kFlipT; ++p) {
+    const double cp = c[p];
+    if (cp == 0.0) continue;
+#pragma unroll
+    for (int r = 0; r < kFlipR; ++r) flip_add(acc[r], cp, xt[(t ^ (1 << p)) + r * kFlipT]);
+  }
+  double s = 0.0;
+#pragma unroll
+  for (int r = 0; r < kFlipR; ++r) {
+    const uint32_t i = e0 + (uint32_t)(t + r * kFlipT);
+    const double h = w0 * d[r];
+    const double2 yv = make_double2(fma(w1, acc[r].x, h * xo[r].x) * invk,
+                                    fma(w1, acc[r].y, h * xo[r].y) * invk);
+    if (act && i < ne) {
+      typedef double dv2 __attribute__((ext_vector_type(2)));
+      __builtin_nontemporal_store(dv2{yv.x, yv.y}, reinterpret_cast<dv2*>(y) + i);
+      s += (xo[r].x * yv.x + xo[r].y * yv.y) * invk;
+    }
+  }
+  __syncthreads();  // the tile's readers are done: its space serves the sums
+  block_partial<kFlipT / 64>(s, gr, reinterpret_cast<double*>(xt), L, tile);
 }
 
 // ---- w = y - alpha_k v_k - beta_{k-1} v_{k-1}, stored as V_{k+1}; partials of ||w||^2
@@ -245,7 +386,7 @@ __global__ __launch_bounds__(64 * W) void k_b_axpy(BLaunch L, int k) {
       s += wr * wr + wi * wi;
     }
   }
-  block_partial<W>(s, gr, red, L, lb);
+  block_partial<W>(s, gr, red, L, lb - gr.block0);
 }
 
 // ---- psi = sum_l coef_l V_l; partials of ||psi||^2
@@ -278,14 +419,14 @@ __global__ __launch_bounds__(64 * W) void k_b_combine(BLaunch L) {
       s += ar * ar + ai * ai;
     }
   }
-  block_partial<W>(s, gr, red, L, lb);
+  block_partial<W>(s, gr, red, L, lb - gr.block0);
 }
 
 // Fixed-order sum of instance j's block partials by one wavefront.
-__device__ double slot_sum(const BLaunch& L, const BGroup& gr, int j) {
+__device__ double slot_sum(const BLaunch& L, const BGroup& gr, int j, int nblocks) {
   const int lane = threadIdx.x & 63;
   const double* __restrict__ p = L.part + (int64_t)(gr.slot0 + j) * L.pstride;
-  double s = thread_partials_chunked<64, 16>(p, gr.nblocks, lane);
+  double s = thread_partials_chunked<64, 16>(p, nblocks, lane);
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
   return lane_read(s, 0);
@@ -337,7 +478,7 @@ __global__ __launch_bounds__(64) void k_b_scalars(BLaunch L, int mode, int k) {
   const int64_t sb = (int64_t)slot * kMaxM;
   const double dt = L.st->dt;
   if (mode == kBStart) {
-    const double b0 = sqrt(slot_sum(L, gr, j));
+    const double b0 = sqrt(slot_sum(L, gr, j, gr.nblocks));
     if (lane == 0) {
       L.S.beta0[slot] = b0;
       L.S.inv[sb] = (b0 > 0.0) ? 1.0 / b0 : 0.0;
@@ -355,14 +496,14 @@ __global__ __launch_bounds__(64) void k_b_scalars(BLaunch L, int mode, int k) {
   if (L.S.done[slot]) return;
   const int mcap = L.S.mcap[slot];
   if (mode == kBAlpha) {
-    const double a = slot_sum(L, gr, j);
+    const double a = slot_sum(L, gr, j, L.low_blocks ? gr.sblocks : gr.nblocks);
     if (lane == 0) L.S.alpha[sb + k] = a;
     wave_sync();
     if (k == mcap - 1) finish_slot(L, slot, k + 1, dt, lds, false, make_double2(0.0, 0.0), 0);
     return;
   }
   // kBBeta
-  const double b = sqrt(slot_sum(L, gr, j));
+  const double b = sqrt(slot_sum(L, gr, j, gr.nblocks));
   if (lane == 0) L.S.beta[sb + k] = b;
   wave_sync();
   const double al = (lane <= k) ? L.S.alpha[sb + lane] : 0.0;
@@ -455,6 +596,12 @@ hipError_t batch_scalars(const BLaunch& L, int mode, int k, hipStream_t s) {
 }
 
 hipError_t batch_spmm(const BLaunch& L, int k, hipStream_t s) {
+  if (L.low_blocks) {
+    if (L.high_blocks)
+      hipLaunchKernelGGL(k_b_high, dim3(L.high_blocks), dim3(kFlipT), 0, s, L, k);
+    hipLaunchKernelGGL(k_b_low, dim3(L.low_blocks), dim3(kFlipT), 0, s, L, k);
+    return hipGetLastError();
+  }
   CFET_ROW_LAUNCH(k_b_spmm, L, k);
   return hipGetLastError();
 }

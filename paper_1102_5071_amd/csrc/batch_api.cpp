@@ -41,6 +41,7 @@ struct cfet_batch {
   std::vector<void*> allocs;       // operator arrays
   int64_t ntot = 0;
   int total_blocks = 0;
+  int low_blocks = 0, high_blocks = 0;  // flip sweeps (0: k_b_spmm)
   int64_t pstride = 0;             // partial sums per instance (most blocks of a group)
   int unroll = 1;                  // rows per lane and pass (autotuned)
   int waves = cfet::kBatchDefaultWaves;  // wavefronts per block of the row kernels (autotuned)
@@ -119,6 +120,27 @@ void free_batch(cfet_batch* b) {
 static_assert(sizeof(cfet_batch_stats_t) == 168 && offsetof(cfet_batch_stats_t, tune_us) == 72,
               "cfet_batch_stats_t layout is part of the ABI");
 
+// True if every row of H holds exactly the flips of the same single row bits,
+// with the same real factors (f, by row bit).
+bool single_flips(const HostCSR& H, std::vector<double>* f) {
+  const int64_t n = H.n;
+  if (n < 2 || (n & (n - 1)) != 0) return false;
+  f->assign(63 - __builtin_clzll(uint64_t(n)), 0.0);
+  const int64_t len = H.rp[1] - H.rp[0];
+  for (int64_t r = 0; r < n; ++r) {
+    if (H.rp[r + 1] - H.rp[r] != len) return false;
+    for (int64_t e = H.rp[r]; e < H.rp[r + 1]; ++e) {
+      const uint64_t off = uint64_t(H.col[e]) ^ uint64_t(r);
+      if (off == 0 || (off & (off - 1)) != 0) return false;
+      double& v = (*f)[size_t(__builtin_ctzll(off))];
+      if (r == 0 && v == 0.0) v = H.val[2 * e];
+      else if (r == 0) return false;  // an entry given twice
+      if (v == 0.0 || H.val[2 * e] != v || H.val[2 * e + 1] != 0.0) return false;
+    }
+  }
+  return true;
+}
+
 // Block layout of the row kernels for a given unroll: fills rows_per_block,
 // nblocks, block0 and returns the total number of blocks.
 int layout_blocks(std::vector<BGroup>& G, int unroll, int waves) {
@@ -143,6 +165,8 @@ BLaunch launch_of(const cfet_batch* b) {
   L.Y = b->Y;
   L.part = b->part;
   L.pstride = b->pstride;
+  L.low_blocks = b->low_blocks;
+  L.high_blocks = b->high_blocks;
   L.waves = b->waves;
   L.S = b->S;
   L.st = b->st;
@@ -397,6 +421,10 @@ CFET_API int cfet_batch_create(int32_t nops, const cfet_csr* ops, int32_t ninst,
     b->user_off.resize(ninst);
     for (int slot = 0; slot < ninst; ++slot) b->user_off[slot] = off[b->inst_of[slot]];
   }
+  // the flip sweeps serve a batch if they serve all of its groups
+  bool flips = true;
+  std::map<Key, std::vector<double>> flip_of;  // factor of each row bit's flip
+  std::vector<double*> diag_r;                 // real diagonals (freed if unused)
   // shared operators, one per key
   std::map<Key, std::tuple<int64_t*, uint32_t*, double2*>> shared;
   int slot = 0;
@@ -463,6 +491,9 @@ CFET_API int cfet_batch_create(int32_t nops, const cfet_csr* ops, int32_t ninst,
         break;
       }
       shared[key] = std::make_tuple(drp, dcol, dval);
+      std::vector<double> f;
+      flips = flips && sh < 0 && hk.size() == 1 && single_flips(mats[hk[0]], &f);
+      flip_of[key] = f;
     }
     BGroup g{};
     g.n = n;
@@ -508,6 +539,32 @@ CFET_API int cfet_batch_create(int32_t nops, const cfet_csr* ops, int32_t ninst,
       if (e == hipSuccess)
         e = hipMemcpy(dd, diag.data(), diag.size() * sizeof(double), hipMemcpyHostToDevice);
       g.diag = dd;
+      // the flip sweeps: factors by element bit, real diagonal
+      int lb = 0;
+      while ((1 << lb) < B) ++lb;
+      g.nv = lb;
+      while ((int64_t(1) << (g.nv - lb)) < n) ++g.nv;
+      flips = flips && !any_off && g.nv <= cfet::kFlipMaxBits;
+      for (size_t q = 1; q < diag.size() && flips; q += 2) flips = diag[q] == 0.0;
+      if (flips && e == hipSuccess) {
+        std::vector<double> cf(24, 0.0), dr(diag.size() / 2);
+        const std::vector<double>& f = flip_of[key];
+        for (size_t i = 0; i < f.size(); ++i) cf[i + size_t(lb)] = f[i];
+        for (size_t q = 0; q < dr.size(); ++q) dr[q] = diag[2 * q];
+        double *dc = nullptr, *dv = nullptr;
+        e = dalloc(&dc, cf.size());
+        if (e == hipSuccess) b->allocs.push_back(dc);
+        if (e == hipSuccess) e = dalloc(&dv, dr.size());
+        if (e == hipSuccess) diag_r.push_back(dv);
+        if (e == hipSuccess)
+          e = hipMemcpy(dc, cf.data(), cf.size() * sizeof(double), hipMemcpyHostToDevice);
+        if (e == hipSuccess)
+          e = hipMemcpy(dv, dr.data(), dr.size() * sizeof(double), hipMemcpyHostToDevice);
+        g.coef = dc;
+        g.diagr = dv;
+        g.sblocks = std::max(1, 1 << std::max(0, g.nv - cfet::kFlipBits));
+        g.hblocks = g.nv - cfet::kFlipBits > cfet::kFlipGather ? g.sblocks : 0;
+      }
       if (e == hipSuccess && any_off) {
         int64_t* drp = nullptr;
         int32_t* dcol = nullptr;
@@ -534,10 +591,31 @@ CFET_API int cfet_batch_create(int32_t nops, const cfet_csr* ops, int32_t ninst,
     voff += n * g.B;
     slot = end;
   }
+  // of the two forms of the diagonals the batch keeps the one it uses
+  for (double* p : diag_r) {
+    if (flips && rc == CFET_OK) b->allocs.push_back(p);
+    else (void)hipFree(p);
+  }
   if (rc != CFET_OK) {
     g_berr = b->err;
     free_batch(b);
     return rc;
+  }
+  for (auto& g : b->groups) {
+    if (!flips) {
+      g.diagr = nullptr;
+      g.sblocks = g.hblocks = 0;
+      continue;
+    }
+    void* const dd = const_cast<double2*>(g.diag);
+    b->allocs.erase(std::remove(b->allocs.begin(), b->allocs.end(), dd), b->allocs.end());
+    (void)hipFree(dd);
+    g.diag = nullptr;
+    g.sblock0 = b->low_blocks;
+    g.hblock0 = b->high_blocks;
+    b->low_blocks += g.sblocks;
+    b->high_blocks += g.hblocks;
+    b->pstride = std::max<int64_t>(b->pstride, g.sblocks);
   }
   b->ntot = voff;
   // partial-sum rows sized for the layout with the most blocks (the smallest

@@ -26,6 +26,11 @@ constexpr int kBatchWaveChoices[] = {2, 4, 8};
 constexpr int kBatchDefaultWaves = 4;
 constexpr int kBatchMaxK1 = 8;      // 1 + driven terms
 
+// Tiles of the flip sweeps (batch.hip): elements of a packed vector.
+constexpr int kFlipBits = 12;
+constexpr int kFlipMaxBits = 21;    // packed elements of a group they serve
+constexpr int kFlipGather = 3;      // bits above a tile that the low sweep gathers itself
+
 struct BGroup {
   int64_t n;            // rows
   int64_t voff;         // element offset of the group's vectors
@@ -36,7 +41,12 @@ struct BGroup {
   int block0;           // first block of the group in that grid
   int slot0;            // first instance slot of the group
   int shared_h0;        // 1: H0 is term 0 of the shared operator
+  int nv;               // flip sweeps: n * B = 2^nv elements,
+  int sblocks, sblock0; //   tiles of the low sweep (all groups) and
+  int hblocks, hblock0; //   of the high sweep (0: the low sweep gathers)
   int pad;
+  const double* coef;   // flip sweeps: factor of the flip of element bit v < 24
+  const double* diagr;  // flip sweeps: [n][B] real H0 diagonal
   const int64_t* rowptr;  // shared operator, n + 1 row pointers
   const uint32_t* colt;   // column | term << kTermShift
   const double2* val;
@@ -87,6 +97,8 @@ struct BLaunch {
   double2* Y;            // H v_k
   double* part;          // [slot][pstride] partial sums: instance slot, block of its group
   int64_t pstride;
+  int low_blocks;        // flip sweeps: blocks of the low sweep (0: k_b_spmm) and
+  int high_blocks;       //   of the high sweep
   int waves;             // wavefronts per block of the row kernels (2, 4 or 8)
   BSlots S;
   BState* st;

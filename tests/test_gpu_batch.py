@@ -291,3 +291,32 @@ def test_status_starts_clear_without_autotune():
             assert P.stats()["status"] == 0
     with B.BatchPropagator(ops, insts, autotune=False) as P:
         assert P.stats()["status"] == 0
+
+
+@pytest.mark.parametrize("sizes", [
+    [(1, 3), (2, 1), (3, 2), (6, 64), (9, 9)],     # within one tile
+    [(11, 2), (12, 1), (12, 2), (13, 1), (10, 7)],  # a full tile, the first flip above it
+    [(15, 1), (13, 8), (14, 3)],                    # flips above the tile gathered
+    [(16, 1), (13, 12), (12, 65)],                  # the second sweep, fewest and many instances
+    [(16, 32), (17, 2)],                            # the largest groups it serves
+    [(16, 64)],                                     # one bit more: every row's neighbours
+], ids=str)
+def test_flip_sweeps_match_oracle(sizes):
+    rng = np.random.default_rng(7)
+    ops, insts = [], []
+    for L, count in sizes:
+        ops.append(I.sigma_x_sum(L, rng.uniform(0.5, 1.5, L)))
+        hk = len(ops) - 1
+        for j in range(count):
+            ops.append(I.ising_chain(L, 1.0, rng.uniform(-1, 1, L)))
+            psi0 = I.random_state(1 << L, rng)
+            insts.append({"h0": len(ops) - 1, "hk": [hk],
+                          "drives": [{"kind": "cos", "A": float(rng.uniform(0.2, 1.5)),
+                                      "omega": float(rng.uniform(0.5, 3.0)), "phi": 0.3}],
+                          "psi0": 0 * psi0 if L < 13 and j == 1 else psi0})
+    args = (0.1, 0.03, 1, "CF4:2", 24, 1e-10)
+    refs, rmv = oracle_run(ops, insts, *args)
+    outs, mv, _ = gpu_run(ops, insts, *args)
+    assert list(mv) == list(rmv)
+    for r, o in zip(refs, outs):
+        assert rel(o, r) <= 1e-11
