@@ -39,9 +39,8 @@ DEFAULT_CHUNK = {"hydrogen": 10, "ising": 50, "heisenberg": 1, "batched": 0, "ad
 DEFAULT_STEPS = {"hydrogen": (200, 20), "ising": (1000, 100), "heisenberg": (20, 2),
                  "batched": (200, 20), "adjoint": (200, 20)}
 # the roofline each plain workload's dominant kernel is measured against: the
-# Heisenberg chain's SpMV streams its vectors and layout from HBM (1.7 GB of
-# counted traffic per SpMV on the split layout, 13 GB in complex-CSR terms;
-# its first pass runs below that ceiling, held by per-slice latency chains);
+# Heisenberg chain's two sweeps per Lanczos iteration stream their vectors from
+# HBM (8.5 vectors of 268 MB; 13 GB for the product alone in complex-CSR terms);
 # the hydrogen and Ising operators and Krylov bases stay in the caches and
 # their persistent kernels wait on grid-wide round trips
 BOUND = {"heisenberg": "hbm", "hydrogen": "latency", "ising": "latency"}
@@ -63,7 +62,7 @@ def log(msg):
 
 
 def spmv_algorithmic_bytes(dim, nnz_total, ncsr):
-    """Bytes one weighted SpMV must move: each stored non-zero once (16 B value
+    """Bytes one weighted SpMV in CSR form must move: each stored non-zero once (16 B value
     + 4 B column), the row pointers of every CSR once, x read once and y
     written once."""
     return 20 * nnz_total + 8 * (dim + 1) * ncsr + 32 * dim
@@ -75,6 +74,12 @@ def exponential_algorithmic_bytes(dim, nnz_total, ncsr, m):
     (read m basis vectors, write psi: (m+1)*16 B per row)."""
     return (m * spmv_algorithmic_bytes(dim, nnz_total, ncsr) + (m - 1) * 64 * dim
             + (m + 1) * 16 * dim)
+
+
+def site_form(matrix_bytes, dim):
+    """True when the multi-kernel path runs on the site-term form: it stores at
+    most one double per row and its terms, every other layout more."""
+    return matrix_bytes <= 8 * dim + 65536
 
 
 def measured_traffic(kernel, key, chunk):
@@ -377,7 +382,7 @@ def run_adjoint(args):
     grad_bytes = 3 * N * s_exp * exponential_algorithmic_bytes(p.dim, nnz_total, 1 + len(p.Hk),
                                                                 min(p.m, p.dim))
     grad_achieved = grad_bytes / (timed_ms * 1e-3) / 1e9 if timed_ms > 0 else None
-    log(f"k_propagate in the gradient: {launches} launches, {timed_ms:.1f} ms, "
+    log(f"persistent launches in the gradient: {launches} launches, {timed_ms:.1f} ms, "
         f"{grad_bytes / 1e9:.1f} GB algorithmic -> {grad_achieved:.0f} GB/s")
     # central differences of a few components with the GPU forward map: h = 1e-6
     # (rounding-limited) and the fourth-order stencil at h = 1e-3
@@ -428,7 +433,8 @@ def run_adjoint(args):
                    "gradient_over_forward_time": round(elapsed / el_f, 3),
                    "fd_max_rel_error": fd_err, "fd4_max_rel_error": fd4_err, "F": F},
         "roofline": ({"bound": "latency",
-                      "kernel": "k_propagate (forward, recomputation and adjoint exponentials)",
+                      "kernel": "k_site_team (forward, recomputation and adjoint exponentials; "
+                                "bytes in CSR terms)",
                       "achieved": round(grad_achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                       "frac": round(grad_achieved / HBM_PEAK_GBS, 4), "traffic": None,
                       "bytes_per_launch": grad_bytes / max(1, launches), "launches": launches,
@@ -610,7 +616,15 @@ def run_plain(args):
     extra = {}
     if path == "multi":
         kernel = B.SPMV_KERNEL_NAMES[stp["layout"]]
-        if layout in ("sell_uniform", "sell_split"):
+        if site_form(stp["matrix_bytes"], p.dim):
+            # one iteration: z_{k-1}, u_{k-1}, u_{k-2} read, u_k, z_k written
+            # (Chebyshev term: x, t_{k-2} read, t_k written, psi at every third)
+            kernel = "k_sweep"
+            layout = "site"
+            key += "_site"
+            bytes_per_launch = stp["matrix_bytes"] + (59 if cheb else 80) * p.dim
+            extra["csr_equivalent_bytes_per_spmv"] = csr_bytes
+        elif layout in ("sell_uniform", "sell_split"):
             # the stored bytes of this layout (per-slice shared entries once)
             # plus x read once and y written once
             bytes_per_launch = stp["matrix_bytes"] + 32 * p.dim
@@ -623,6 +637,12 @@ def run_plain(args):
             # the Chebyshev path times its applies (no Lanczos epilogue)
             key += "_cheb"
             kernel = {"k_lz_spmv": "k_apply", "k_sell_lz_spmv": "k_sell_apply"}.get(kernel, kernel)
+    elif args.workload == "ising" and p.dim <= 1 << 14 and not args.path and not args.layout:
+        # site terms: per exponential the basis and the state
+        # (u_k written and read back, psi written); the operator is in registers
+        kernel = "k_site_one" if p.dim <= 1 << 10 else "k_site_team"
+        layout = "site"
+        bytes_per_launch = chunk * s * 32 * m_eff * p.dim
     else:
         kernel = "k_propagate"
         bytes_per_launch = chunk * s * exponential_algorithmic_bytes(p.dim, nnz_total, ncsr, m_eff)

@@ -122,6 +122,13 @@ typedef struct {
 #define CFET_FORCE_COOPERATIVE 0x40u  /* if the rows fit the co-resident blocks */
 /* A forced persistent path that does not fit falls back to the multi-kernel
  * path; cfet_stats reports the path taken. */
+/* Without a path or layout flag, an operator that is a sum of site terms -- n =
+ * 2^b rows, every off-diagonal entry one of a few (row XOR offset) with a value
+ * that depends on the parity of a few row bits, a real diagonal in one of the
+ * terms -- runs from that compact form on kernels of its own: persistent up to
+ * 2^14 rows (paths 2 and 3), two sweeps per Lanczos iteration from 2^16 rows
+ * (path 1; also cfet_apply and cfet_propagate_chebyshev there).  Detection runs
+ * on the host at cfet_create; same results up to the order of summation. */
 /* Store the operator in sliced-ELL form (64-row slices, column-major, driven
  * terms first in each row) for the multi-kernel path.  Large dimensions
  * (n > 2^22, where only the multi-kernel path runs) default to
@@ -189,7 +196,10 @@ typedef struct {
                                 CFET_NO_REORDER) */
   int64_t matrix_bytes;      /* stored operator bytes one application of that layout
                                 reads (values, columns, masks, row and slice data;
-                                padding excluded) */
+                                padding excluded).  Where the multi-kernel path runs
+                                on the site-term form: that form's bytes, at most 8
+                                per row and its terms; layout then tells what the
+                                dimension alone would select */
 } cfet_stats_t;
 
 /* Build a context for H(t) = H0 + sum_k f_k(t) Hk[k], k < nterms
@@ -348,7 +358,8 @@ CFET_API const char *cfet_last_error(const cfet_ctx *c);
 /* Kernel timing for measurement: with enable != 0, cfet_propagate records a
  * HIP event pair on the caller's stream around every launch of its dominant
  * kernel -- the Lanczos SpMV on the multi-kernel path (both launches of a
- * split layout between one event pair; the apply of each term with
+ * split layout between one event pair; on the site-term form the two sweeps
+ * of an iteration, its vector update included; the apply of each term with
  * cfet_propagate_chebyshev), the whole persistent kernel on the
  * single-workgroup and cooperative paths, also its launches inside
  * cfet_gradient -- (up to max_launches

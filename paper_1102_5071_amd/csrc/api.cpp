@@ -375,48 +375,64 @@ int propagate_persistent(cfet_ctx* c, void* psi_dev, double t0, double dt, int64
     harvest_events(c);
   }
   const size_t need = size_t(nsteps) * sc.s * nt1;
-  hipError_t e;
-  // the pinned staging buffer is reused: wait for its previous upload
-  if (c->wts_pending) {
-    e = hipEventSynchronize(c->wts_copied);
-    if (e != hipSuccess) return hip_fail(c, e, "wait for the weight upload");
-    c->wts_pending = false;
-  }
-  if (need > c->h_wts_cap) {
-    if (c->h_wts) (void)hipHostFree(c->h_wts);
-    c->h_wts = nullptr;
-    c->h_wts_cap = 0;
-    e = hipHostMalloc(&c->h_wts, need * sizeof(double));
-    if (e != hipSuccess) {
-      (void)hipGetLastError();
-      return fail(c, CFET_ENOMEM, "cannot allocate the pinned weight table");
-    }
-    c->h_wts_cap = need;
-  }
-  if (need > c->wts_cap) {
-    if (c->d_wts) (void)hipFree(c->d_wts);
-    c->d_wts = nullptr;
-    c->wts_cap = 0;
-    e = hipMalloc(&c->d_wts, need * sizeof(double));
-    if (e != hipSuccess) {
-      (void)hipGetLastError();
-      return fail(c, CFET_ENOMEM, "cannot allocate the device weight table");
-    }
-    c->wts_cap = need;
-  }
+  hipError_t e = hipSuccess;
   std::vector<double> a(sc.s), b(sc.s * c->nterms);
-  for (int64_t n = 0; n < nsteps; ++n) {
-    cfet::step_weights(sc, c->drives, t0 + double(n) * dt, dt, a.data(), b.data());
-    double* row = c->h_wts + size_t(n) * sc.s * nt1;
-    for (int i = 0; i < sc.s; ++i) {
-      row[i * nt1] = a[i];
-      for (int k = 0; k < c->nterms; ++k) row[i * nt1 + 1 + k] = b[i * c->nterms + k];
+  auto fill = [&](double* table) {
+    for (int64_t n = 0; n < nsteps; ++n) {
+      cfet::step_weights(sc, c->drives, t0 + double(n) * dt, dt, a.data(), b.data());
+      double* row = table + size_t(n) * sc.s * nt1;
+      for (int i = 0; i < sc.s; ++i) {
+        row[i * nt1] = a[i];
+        for (int k = 0; k < c->nterms; ++k) row[i * nt1 + 1 + k] = b[i * c->nterms + k];
+      }
     }
+  };
+  // The kernel of the site-operator form takes a short call's weights in its
+  // arguments and writes the statistics to the pinned copy itself: no copy
+  // precedes or follows it.  (One step on 2^10 rows: 62.7 us with the copies,
+  // 54.4 without; a new state's first call 161 and 87.)  Longer tables would
+  // cost more as arguments, which the kernel reads from host memory, than the
+  // copy.  The gradient reads the table again, so its calls upload it.
+  double small[cfet::kSiteInlineW];
+  const bool inline_w =
+      c->site.ok && !export_T && !save && need <= size_t(cfet::kSiteInlineW);
+  if (inline_w) {
+    fill(small);
+  } else {
+    // the pinned staging buffer is reused: wait for its previous upload
+    if (c->wts_pending) {
+      e = hipEventSynchronize(c->wts_copied);
+      if (e != hipSuccess) return hip_fail(c, e, "wait for the weight upload");
+      c->wts_pending = false;
+    }
+    if (need > c->h_wts_cap) {
+      if (c->h_wts) (void)hipHostFree(c->h_wts);
+      c->h_wts = nullptr;
+      c->h_wts_cap = 0;
+      e = hipHostMalloc(&c->h_wts, need * sizeof(double));
+      if (e != hipSuccess) {
+        (void)hipGetLastError();
+        return fail(c, CFET_ENOMEM, "cannot allocate the pinned weight table");
+      }
+      c->h_wts_cap = need;
+    }
+    if (need > c->wts_cap) {
+      if (c->d_wts) (void)hipFree(c->d_wts);
+      c->d_wts = nullptr;
+      c->wts_cap = 0;
+      e = hipMalloc(&c->d_wts, need * sizeof(double));
+      if (e != hipSuccess) {
+        (void)hipGetLastError();
+        return fail(c, CFET_ENOMEM, "cannot allocate the device weight table");
+      }
+      c->wts_cap = need;
+    }
+    fill(c->h_wts);
+    e = hipMemcpyAsync(c->d_wts, c->h_wts, need * sizeof(double), hipMemcpyHostToDevice, st);
+    if (e == hipSuccess) e = hipEventRecord(c->wts_copied, st);
+    if (e != hipSuccess) return hip_fail(c, e, "upload the weight table");
+    c->wts_pending = true;
   }
-  e = hipMemcpyAsync(c->d_wts, c->h_wts, need * sizeof(double), hipMemcpyHostToDevice, st);
-  if (e == hipSuccess) e = hipEventRecord(c->wts_copied, st);
-  if (e != hipSuccess) return hip_fail(c, e, "upload the weight table");
-  c->wts_pending = true;
   int nblocks = 1;
   if (path == 3 && !c->site.ok) {
     nblocks = c->coop_blocks;
@@ -447,7 +463,8 @@ int propagate_persistent(cfet_ctx* c, void* psi_dev, double t0, double dt, int64
   pa.real_vals = c->real_vals ? 1 : 0;
   pa.n = c->n;
   pa.nterms = c->nterms;
-  pa.wts = c->d_wts;
+  pa.wts = inline_w ? small : c->d_wts;
+  pa.stats_out = c->site.ok ? c->stats_host : nullptr;
   pa.s = sc.s;
   pa.nsteps = nsteps;
   pa.m = m;
@@ -468,14 +485,14 @@ int propagate_persistent(cfet_ctx* c, void* psi_dev, double t0, double dt, int64
   pa.export_each = (export_T || export_Y) ? 1 : 0;
   const bool timed = c->profiling && c->events.used < c->events.cap;
   if (timed) (void)hipEventRecord(c->events.begin[c->events.used], st);
-  e = c->site.ok ? cfet::launch_site(c->site, pa, st)
+  e = c->site.ok ? cfet::launch_site(c->site, pa, st, inline_w ? int(need) : 0)
                  : cfet::launch_persistent(pa, path == 2 ? c->preset_single : c->preset_coop,
                                            path == 2, nblocks, st);
   if (timed && e == hipSuccess) {
     (void)hipEventRecord(c->events.end[c->events.used], st);
     c->events.used += 1;
   }
-  if (e == hipSuccess)
+  if (e == hipSuccess && !c->site.ok)
     e = hipMemcpyAsync(c->stats_host, c->stats, sizeof(DevStats), hipMemcpyDeviceToHost, st);
   if (e != hipSuccess) return hip_fail(c, e, "persistent propagation launch");
   c->last_stream = st;

@@ -350,6 +350,8 @@ struct PersistArgs {
                             // export_Y + e*m*n) instead of the last one only
   int rev;                  // site-operator form only: 1 takes the call's exponentials (and
                             // their weights and records) from the last to the first
+  DevStats* stats_out;      // site-operator form only: pinned host copy of the statistics,
+                            // written at the end of the launch (null: none)
   int basis_each;           // site-operator form only: 1 keeps the basis of every
                             // exponential e, its vector j >= 0 at basis + (e*m + j)*n
   int real_vals;            // 1: every imaginary part of val is 0 (real-valued kernels)

@@ -174,8 +174,11 @@ struct DevSite {
   unsigned long long* count = nullptr;
 };
 
+constexpr int kSiteInlineW = 32;  // weights a launch takes in its arguments, at most
 struct SiteArgs {
   PersistArgs p;
+  int inline_w;            // weights in w (0: in p.wts)
+  double w[kSiteInlineW];
   const PElem* e;
   int nfar[2], set_term[2];
   const double* diag;
@@ -189,6 +192,7 @@ struct SiteArgs {
 // Sets up the plan's kernel; *fits: a launch's blocks are co-resident.
 hipError_t site_prepare(const SitePlan& P, bool real, int num_cus, bool* fits);
 // A whole call (see PersistArgs; basis, psi, wts and the exports are used).
-hipError_t launch_site(const DevSite& S, const PersistArgs& args, hipStream_t st);
+// host_wts: p.wts is a host table of nwts <= kSiteInlineW weights
+hipError_t launch_site(const DevSite& S, const PersistArgs& args, hipStream_t st, int nwts = 0);
 
 }  // namespace cfet

@@ -338,7 +338,7 @@ __device__ __forceinline__ void site_run(const SiteArgs& A, int rank, double2* x
     for (int iq = 0; ok && iq < A.p.s; ++iq) {
       const int i = A.p.rev ? iq : A.p.s - 1 - iq;
       const int64_t eidx = step * A.p.s + (A.p.s - 1 - i);
-      const double* const wts = A.p.wts + ((size_t)step * A.p.s + i) * nt1;
+      const double* const wts = (A.inline_w ? A.w : A.p.wts) + ((size_t)step * A.p.s + i) * nt1;
       // the sets' weights and the diagonal's
       const double ws0 = WTD ? 1.0 : wts[A.set_term[0]];
       const double ws1 = NS > 1 ? wts[A.set_term[1]] : 0.0;
@@ -717,10 +717,13 @@ __device__ __forceinline__ void site_run(const SiteArgs& A, int rank, double2* x
     }
     if (tm.on)
       for (int q = 0; q < 4; ++q) st->seg[q] += tm.acc[q];
+    if (A.p.stats_out) *A.p.stats_out = *st;
   }
-  if (!ok && t == 0)
+  if (!ok && t == 0) {
     __hip_atomic_store(&A.p.stats->status, (int)CFET_EDEVICE, __ATOMIC_RELAXED,
                        __HIP_MEMORY_SCOPE_AGENT);
+    if (A.p.stats_out) A.p.stats_out->status = (int)CFET_EDEVICE;
+  }
 }
 
 template <int T, int R, int MODE, bool RV>
@@ -939,9 +942,14 @@ hipError_t site_prepare(const SitePlan& P, bool real, int num_cus, bool* fits) {
   return hipSuccess;
 }
 
-hipError_t launch_site(const DevSite& S, const PersistArgs& args, hipStream_t st) {
+hipError_t launch_site(const DevSite& S, const PersistArgs& args, hipStream_t st, int nwts) {
   SiteArgs A{};
   A.p = args;
+  if (nwts > 0) {
+    A.inline_w = 1;
+    std::copy(args.wts, args.wts + nwts, A.w);
+    A.p.wts = nullptr;
+  }
   A.e = S.e;
   for (int s = 0; s < 2; ++s) {
     A.nfar[s] = S.plan.nfar[s];

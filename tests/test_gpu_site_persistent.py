@@ -156,6 +156,22 @@ def test_gradient_batches_match_one_exponential_at_a_time(L, N, scheme, m):
     assert np.max(np.abs(g - go)) <= 1e-8 * np.max(np.abs(go))
 
 
+@pytest.mark.parametrize("L", [8, 12])
+def test_short_and_long_calls_agree(L):
+    # weights in the launch's arguments (short calls) and in a device table
+    H0, Hk, drives, psi0 = chain("spins", L, L)
+    with B.Propagator(H0, Hk, drives) as P:
+        a, b = dev(psi0), dev(psi0)
+        P.propagate(a, 0.0, 0.0625, 8, "CF4:2", 12)       # 48 weights
+        count = P.stats()["matvecs"]                      # (the state spans few vectors)
+        assert count > 0
+        for q in range(8):                                # 6 weights a call
+            P.propagate(b, q * 0.0625, 0.0625, 1, "CF4:2", 12)
+        assert P.stats()["matvecs"] == 2 * count
+        torch.cuda.synchronize()
+        assert torch.equal(a, b)
+
+
 def test_two_streams_and_two_contexts():
     # two contexts in flight on two streams, teams of 16 and 8 blocks
     jobs = []
