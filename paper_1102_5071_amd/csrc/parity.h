@@ -180,7 +180,7 @@ struct SiteArgs {
   int inline_w;            // weights in w (0: in p.wts)
   double w[kSiteInlineW];
   const PElem* e;
-  int nfar[2], set_term[2];
+  int set_term[2];
   const double* diag;
   int diag_term;
   int tl, blocks;

@@ -313,10 +313,9 @@ __device__ __forceinline__ void site_run(const SiteArgs& A, int rank, double2* x
     for (int s = 0; s < NS; ++s)
 #pragma unroll
       for (int f = 0; f < NG; ++f)
-        if (f < A.nfar[s])
 #pragma unroll
-          for (int r = 0; r < R; ++r)
-            g[s][f][r] = shared_load(base, (row0 + (uint32_t)(r * T)) ^ fo[s][f], n);
+        for (int r = 0; r < R; ++r)
+          g[s][f][r] = shared_load(base, (row0 + (uint32_t)(r * T)) ^ fo[s][f], n);
   };
   // Tags grow by one per exchange.  The sums use two sets of records in turn: a
   // block may post its next sums while another still reads the last ones, but
@@ -490,7 +489,7 @@ __device__ __forceinline__ void site_run(const SiteArgs& A, int rank, double2* x
                 acc_fma<RV>(acc[s][r], w_x[r], lds_at(xa + (r ^ 1) * T * 16));
           }
           // (with two rows, few loads at a time: more would spill registers)
-          constexpr int Q = R == 1 ? 8 : 2;
+          constexpr int Q = R == 1 ? 8 : MODE == kOneSet ? 3 : 2;
 #pragma unroll
           for (int q0 = 0; q0 < Sl::lds(s); q0 += Q) {
             double2 x[Q][R];
@@ -521,7 +520,6 @@ __device__ __forceinline__ void site_run(const SiteArgs& A, int rank, double2* x
           for (int s = 0; s < NS; ++s)
 #pragma unroll
             for (int f = 0; f < NF; ++f) {
-              if (f >= A.nfar[s]) continue;
 #pragma unroll
               for (int r = 0; r < R; ++r) {
                 double2 x = g1[s][f][r];
@@ -792,8 +790,6 @@ __global__ __launch_bounds__(T) void k_site_team(SiteArgs A) {
 
 // The launch shapes.  The host fills the table of terms by the slots of the
 // shape it takes, so both come from here.
-constexpr int kTeamFar = 5;  // terms of a set that leave the block, at most
-
 struct Shape {
   const void* fn = nullptr;
   int mv[2], lds[2], reg[2], mix[2], far[2];
@@ -837,8 +833,14 @@ Shape site_shape(const SitePlan& P, bool real) {
       default: return shape_mode<512, 1, 0>(P.mode, real);
     }
   }
-  if (P.T == 256) return shape_mode<256, 1, kTeamFar>(P.mode, real);
-  return P.mode == kOneSet ? shape_of<512, 1, kOneSet, kTeamFar>(real) : Shape{};
+  if (P.T == 512) return P.mode == kOneSet ? shape_of<512, 1, kOneSet, 5>(real) : Shape{};
+  switch (std::max(P.nfar[0], P.nfar[1])) {
+    case 0: case 1: case 2:
+    case 3: return shape_mode<256, 1, 3>(P.mode, real);
+    case 4: return shape_mode<256, 1, 4>(P.mode, real);
+    case 5: return shape_mode<256, 1, 5>(P.mode, real);
+    default: return Shape{};
+  }
 }
 
 size_t site_lds(const SitePlan& P) {
@@ -873,7 +875,9 @@ bool plan_site(const ParityForm& F, SitePlan* P) {
   // 1.2 us (2.6); 2^10, one workgroup with two rows per thread 1.4 (3.0), a team of
   // four 2.0; 2^11, a team of eight 2.1 (4.3), one workgroup with four rows 8.0,
   // as it spills; 2^13, 32 blocks of 256 threads 2.1 (4.3), 16 of 512 2.4; 2^14,
-  // 32 of 512 2.8 (4.6), 32 of 256 with two rows 3.1.  Two sets or several
+  // 32 of 512 2.8 (4.6), 32 of 256 with two rows 3.1 (the teams before the
+  // number of terms that leave the block was fixed at compile time: 2.0 at 2^13
+  // and 2.5 at 2^14 since, without a branch per term).  Two sets or several
   // driven terms need registers for twice the terms: at 2^14 rows they spill
   // and take 15 us (6.0).  Larger teams than 32 do not fit one XCD.  One
   // workgroup is kept up to 2^10 rows also where a team is faster (two sets: 3.4
@@ -894,13 +898,15 @@ bool plan_site(const ParityForm& F, SitePlan* P) {
     return false;
   }
   for (S.tl = nb; (1 << (nb - S.tl)) < S.blocks;) S.tl -= 1;
+  for (int s = 0; s < 2; ++s)
+    for (const ParityTerm& t : sets[s]) S.nfar[s] += (t.off >> S.tl) != 0;
   const Shape K = site_shape(S, F.real);
   if (!K.fn) return false;
   int base = 0;
   for (int s = 0; s < 2; ++s) {
     const int first_lds = base + K.mv[s], first_reg = first_lds + K.lds[s];
     const int mix = first_reg + K.reg[s], first_far = mix + K.mix[s];
-    int lds = 0;
+    int lds = 0, far = 0;
     std::vector<char> used(size_t(first_far + K.far[s]), 0);
     for (const ParityTerm& t : sets[s]) {
       const uint32_t thread = t.off & uint32_t(S.T - 1);
@@ -908,7 +914,7 @@ bool plan_site(const ParityForm& F, SitePlan* P) {
       const bool by_reg = (t.pmask & ((1u << S.tl) - 1u)) / uint32_t(S.T);
       int slot = -1;
       if (t.off >> S.tl) {
-        if (S.nfar[s] < K.far[s]) slot = first_far + S.nfar[s]++;
+        if (far < K.far[s]) slot = first_far + far++;
       } else if (reg != 0 && thread == 0) {
         slot = first_reg + int(reg) - 1;
       } else if (reg != 0) {
@@ -951,10 +957,7 @@ hipError_t launch_site(const DevSite& S, const PersistArgs& args, hipStream_t st
     A.p.wts = nullptr;
   }
   A.e = S.e;
-  for (int s = 0; s < 2; ++s) {
-    A.nfar[s] = S.plan.nfar[s];
-    A.set_term[s] = S.plan.set_term[s];
-  }
+  for (int s = 0; s < 2; ++s) A.set_term[s] = S.plan.set_term[s];
   A.diag = S.diag;
   A.diag_term = S.diag_term;
   A.tl = S.plan.tl;

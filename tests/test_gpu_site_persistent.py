@@ -172,6 +172,22 @@ def test_short_and_long_calls_agree(L):
         assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("L", [11, 12, 13, 14])
+@pytest.mark.parametrize("sites", [[0], [2, -1], [-3, -2, -1]])
+def test_few_driven_sites(L, sites):
+    # fewer terms that leave a workgroup's rows than the kernel has places for
+    X, k = I.sigma_x_sum(L), len(sites)
+    Hk = type(X)(X.n, np.arange(X.n + 1, dtype=X.row_ptr.dtype) * k,
+                 X.col.reshape(-1, L)[:, sites].ravel(), X.val.reshape(-1, L)[:, sites].ravel())
+    H0, _, drives, psi0 = chain("ising", L, L)
+    ref = O.propagate(H0, [Hk], drives, psi0, 0.0, 0.05, 2, "CF4:2", m=12)
+    with B.Propagator(H0, [Hk], drives) as P:
+        psi = dev(psi0)
+        P.propagate(psi, 0.0, 0.05, 2, "CF4:2", 12)
+        assert P.stats()["status"] == 0
+        assert rel(psi.cpu().numpy(), ref) <= 1e-10
+
+
 def test_two_streams_and_two_contexts():
     # two contexts in flight on two streams, teams of 16 and 8 blocks
     jobs = []
