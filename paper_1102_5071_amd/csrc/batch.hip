@@ -4,7 +4,8 @@
 // Per exponential (paper Sec. 8.1, for each instance independently):
 //   START     beta_0 = ||psi||, the instance is idle if psi = 0
 //   for k = 0, 1, ...:
-//     SPMM    y = H_w v_k on all rows, partial sums of Re<v_k, y>
+//     SPMM    y = H_w v_k on all rows, partial sums of Re<v_k, y> (k_b_spmm, or
+//             the flip sweeps k_b_high and k_b_low)
 //     ALPHA   alpha_k; at k = min(m, n) - 1 the basis is complete
 //     AXPY    w = y - alpha_k v_k - beta_{k-1} v_{k-1} (stored unnormalised
 //             as basis vector k + 1), partial sums of ||w||^2

@@ -141,6 +141,13 @@ bool single_flips(const HostCSR& H, std::vector<double>* f) {
   return true;
 }
 
+bool real_diagonal(const HostCSR& H) {
+  for (int64_t r = 0; r < H.n; ++r)
+    for (int64_t e = H.rp[r]; e < H.rp[r + 1]; ++e)
+      if (H.col[e] != r || H.val[2 * e + 1] != 0.0) return false;
+  return true;
+}
+
 // Block layout of the row kernels for a given unroll: fills rows_per_block,
 // nblocks, block0 and returns the total number of blocks.
 int layout_blocks(std::vector<BGroup>& G, int unroll, int waves) {
@@ -421,10 +428,21 @@ CFET_API int cfet_batch_create(int32_t nops, const cfet_csr* ops, int32_t ninst,
     b->user_off.resize(ninst);
     for (int slot = 0; slot < ninst; ++slot) b->user_off[slot] = off[b->inst_of[slot]];
   }
-  // the flip sweeps serve a batch if they serve all of its groups
+  // the flip sweeps (batch.hip) serve a batch if they serve all of its instances
   bool flips = true;
   std::map<Key, std::vector<double>> flip_of;  // factor of each row bit's flip
-  std::vector<double*> diag_r;                 // real diagonals (freed if unused)
+  for (int q = 0; q < ninst && flips; ++q) {
+    const Key& key = order[q].first;
+    const std::vector<int>& hk = std::get<1>(key);
+    flips = std::get<2>(key) < 0 && hk.size() == 1 &&
+            std::get<0>(key) <= (int64_t(1) << cfet::kFlipMaxBits);
+    if (flips && !flip_of.count(key)) {
+      std::vector<double> f;
+      flips = single_flips(mats[hk[0]], &f);
+      flip_of[key] = f;
+    }
+    flips = flips && real_diagonal(mats[inst[order[q].second].h0]);
+  }
   // shared operators, one per key
   std::map<Key, std::tuple<int64_t*, uint32_t*, double2*>> shared;
   int slot = 0;
@@ -435,8 +453,13 @@ CFET_API int cfet_batch_create(int32_t nops, const cfet_csr* ops, int32_t ninst,
     // serves an instance, and a row's B complex values fill whole cache lines
     int same = slot;
     while (same < ninst && order[same].first == key) ++same;
+    // (at most 2^kFlipMaxBits elements on the flip sweeps, which read no
+    // operator that a larger group would share)
+    int most = cfet::kBatchMaxGroup;
+    if (flips)
+      most = int(std::min<int64_t>(most, (int64_t(1) << cfet::kFlipMaxBits) / std::get<0>(key)));
     int take = 1;
-    while (take * 2 <= std::min(same - slot, cfet::kBatchMaxGroup)) take *= 2;
+    while (take * 2 <= std::min(same - slot, most)) take *= 2;
     const int end = slot + take;
     const int t0 = order[slot].second;
     const int64_t n = mats[inst[t0].h0].n;
@@ -491,9 +514,6 @@ CFET_API int cfet_batch_create(int32_t nops, const cfet_csr* ops, int32_t ninst,
         break;
       }
       shared[key] = std::make_tuple(drp, dcol, dval);
-      std::vector<double> f;
-      flips = flips && sh < 0 && hk.size() == 1 && single_flips(mats[hk[0]], &f);
-      flip_of[key] = f;
     }
     BGroup g{};
     g.n = n;
@@ -533,20 +553,19 @@ CFET_API int cfet_batch_create(int32_t nops, const cfet_csr* ops, int32_t ninst,
         }
         rpj[n] = int64_t(ocol.size());
       }
-      double2* dd = nullptr;
-      e = dalloc(&dd, size_t(n) * B);
-      if (e == hipSuccess) b->allocs.push_back(dd);
-      if (e == hipSuccess)
-        e = hipMemcpy(dd, diag.data(), diag.size() * sizeof(double), hipMemcpyHostToDevice);
-      g.diag = dd;
-      // the flip sweeps: factors by element bit, real diagonal
-      int lb = 0;
-      while ((1 << lb) < B) ++lb;
-      g.nv = lb;
-      while ((int64_t(1) << (g.nv - lb)) < n) ++g.nv;
-      flips = flips && !any_off && g.nv <= cfet::kFlipMaxBits;
-      for (size_t q = 1; q < diag.size() && flips; q += 2) flips = diag[q] == 0.0;
-      if (flips && e == hipSuccess) {
+      if (!flips) {
+        double2* dd = nullptr;
+        e = dalloc(&dd, size_t(n) * B);
+        if (e == hipSuccess) b->allocs.push_back(dd);
+        if (e == hipSuccess)
+          e = hipMemcpy(dd, diag.data(), diag.size() * sizeof(double), hipMemcpyHostToDevice);
+        g.diag = dd;
+      } else {
+        // factors by element bit, real diagonal, tiles
+        int lb = 0;
+        while ((1 << lb) < B) ++lb;
+        g.nv = lb;
+        while ((int64_t(1) << (g.nv - lb)) < n) ++g.nv;
         std::vector<double> cf(24, 0.0), dr(diag.size() / 2);
         const std::vector<double>& f = flip_of[key];
         for (size_t i = 0; i < f.size(); ++i) cf[i + size_t(lb)] = f[i];
@@ -555,7 +574,7 @@ CFET_API int cfet_batch_create(int32_t nops, const cfet_csr* ops, int32_t ninst,
         e = dalloc(&dc, cf.size());
         if (e == hipSuccess) b->allocs.push_back(dc);
         if (e == hipSuccess) e = dalloc(&dv, dr.size());
-        if (e == hipSuccess) diag_r.push_back(dv);
+        if (e == hipSuccess) b->allocs.push_back(dv);
         if (e == hipSuccess)
           e = hipMemcpy(dc, cf.data(), cf.size() * sizeof(double), hipMemcpyHostToDevice);
         if (e == hipSuccess)
@@ -591,26 +610,12 @@ CFET_API int cfet_batch_create(int32_t nops, const cfet_csr* ops, int32_t ninst,
     voff += n * g.B;
     slot = end;
   }
-  // of the two forms of the diagonals the batch keeps the one it uses
-  for (double* p : diag_r) {
-    if (flips && rc == CFET_OK) b->allocs.push_back(p);
-    else (void)hipFree(p);
-  }
   if (rc != CFET_OK) {
     g_berr = b->err;
     free_batch(b);
     return rc;
   }
-  for (auto& g : b->groups) {
-    if (!flips) {
-      g.diagr = nullptr;
-      g.sblocks = g.hblocks = 0;
-      continue;
-    }
-    void* const dd = const_cast<double2*>(g.diag);
-    b->allocs.erase(std::remove(b->allocs.begin(), b->allocs.end(), dd), b->allocs.end());
-    (void)hipFree(dd);
-    g.diag = nullptr;
+  for (auto& g : b->groups) {  // (no tiles without the flip sweeps)
     g.sblock0 = b->low_blocks;
     g.hblock0 = b->high_blocks;
     b->low_blocks += g.sblocks;

@@ -299,7 +299,7 @@ def test_status_starts_clear_without_autotune():
     [(15, 1), (13, 8), (14, 3)],                    # flips above the tile gathered
     [(16, 1), (13, 12), (12, 65)],                  # the second sweep, fewest and many instances
     [(16, 32), (17, 2)],                            # the largest groups it serves
-    [(16, 64)],                                     # one bit more: every row's neighbours
+    [(16, 64), (18, 9)],                            # more instances than such a group holds
 ], ids=str)
 def test_flip_sweeps_match_oracle(sizes):
     rng = np.random.default_rng(7)
