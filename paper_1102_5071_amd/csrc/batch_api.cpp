@@ -429,7 +429,7 @@ CFET_API int cfet_batch_create(int32_t nops, const cfet_csr* ops, int32_t ninst,
     for (int slot = 0; slot < ninst; ++slot) b->user_off[slot] = off[b->inst_of[slot]];
   }
   // the flip sweeps (batch.hip) serve a batch if they serve all of its instances
-  bool flips = true;
+  bool flips = b->user_total >= cfet::kFlipMinElements;
   std::map<Key, std::vector<double>> flip_of;  // factor of each row bit's flip
   for (int q = 0; q < ninst && flips; ++q) {
     const Key& key = order[q].first;

@@ -304,7 +304,7 @@ def test_status_starts_clear_without_autotune():
 def test_flip_sweeps_match_oracle(sizes):
     rng = np.random.default_rng(7)
     ops, insts = [], []
-    for L, count in sizes:
+    for L, count in sizes + [(17, 8)]:              # (the sweeps start at 2^20 elements)
         ops.append(I.sigma_x_sum(L, rng.uniform(0.5, 1.5, L)))
         hk = len(ops) - 1
         for j in range(count):
