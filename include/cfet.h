@@ -169,6 +169,13 @@ typedef struct {
  * multi-kernel CSR path; cfet_propagate keeps the SELL layout).  Costs 20
  * bytes per non-zero and 8 per row of device memory. */
 #define CFET_KEEP_CSR 0x4000u
+/* For tests of the persistent kernels on sums of site terms above 2^10 rows,
+ * whose workgroups form a team on one XCD.  SPREAD_TEAM: the team that is taken
+ * where no XCD holds enough of them, spread over the XCDs (same results, bit
+ * for bit).  NO_TEAM: no team forms; every propagation leaves psi as it was and
+ * latches CFET_EDEVICE, after a wait of 1 ms. */
+#define CFET_TEST_SPREAD_TEAM 0x10000u
+#define CFET_TEST_NO_TEAM 0x20000u
 
 typedef struct cfet_ctx cfet_ctx;
 

@@ -1481,6 +1481,8 @@ int cfet_create(const cfet_csr* H0, int32_t nterms, const cfet_csr* Hk, const cf
         if (e == hipSuccess) e = hipMalloc(&c->site.ids, 257 * sizeof(unsigned long long));
         if (e == hipSuccess) e = hipMemset(c->site.ids, 0, 257 * sizeof(unsigned long long));
         c->site.count = c->site.ids + 256;
+        c->site.skew = (flags & CFET_TEST_NO_TEAM) ? 1 : 0;
+        c->site.spread = (flags & CFET_TEST_SPREAD_TEAM) ? 1 : 0;
       }
     }
     if (found && n >= kParityMinN && cfet::plan_parity(form, &c->parity.plan)) {
@@ -1850,6 +1852,7 @@ int cfet_create(const cfet_csr* H0, int32_t nterms, const cfet_csr* Hk, const cf
     e = hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, c->device);
     if (khz <= 0) khz = 100000;
     c->spin_limit = (long long)khz * 1000LL * 10LL;  // 10 s
+    if (flags & CFET_TEST_NO_TEAM) c->spin_limit = khz;  // 1 ms
   }
   if (e == hipSuccess && c->parity.ok) {
     c->parity.nblk = cfet::parity_grid(c->parity.plan, c->num_cus);

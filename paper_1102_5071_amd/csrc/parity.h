@@ -172,6 +172,9 @@ struct DevSite {
   void* rec = nullptr;                // device: 3 * kSiteRecs records
   unsigned long long* ids = nullptr;  // device: XCD of each block of a launch, then the launch counter
   unsigned long long* count = nullptr;
+  // tests: skew 1 makes a team wait for a launch that does not come (until the
+  // wait's limit), spread 1 forms it from the first blocks of the grid
+  int skew = 0, spread = 0;
 };
 
 constexpr int kSiteInlineW = 32;  // weights a launch takes in its arguments, at most
@@ -187,6 +190,7 @@ struct SiteArgs {
   void* rec;
   unsigned long long* ids;
   unsigned long long* count;
+  int skew, spread;        // (DevSite)
 };
 
 // Sets up the plan's kernel; *fits: a launch's blocks are co-resident.

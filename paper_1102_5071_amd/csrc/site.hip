@@ -233,6 +233,35 @@ __device__ __forceinline__ double2 form_u(double2 z, double2 u1, double2 u2, dou
                       fma(c1, z.y, fma(-c2, u1.y, -c3 * u2.y)));
 }
 
+// A wait of this launch has timed out: latch a device error, in the statistics
+// and in their pinned copy, which the next call on the context looks at.
+__device__ __forceinline__ void report_fault(const SiteArgs& A) {
+  __hip_atomic_store(&A.p.stats->status, (int)CFET_EDEVICE, __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_AGENT);
+  if (A.p.stats_out)
+    __hip_atomic_store(&A.p.stats_out->status, (int)CFET_EDEVICE, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// The statistics to their pinned copy (one thread of a launch).  The host
+// clears the copy's status; here it is only ever set, so that a fault another
+// block reports at the same time stays.
+__device__ __forceinline__ void publish_stats(const SiteArgs& A) {
+  DevStats* const st = A.p.stats;
+  DevStats* const out = A.p.stats_out;
+  if (!out) return;
+  out->exponentials = st->exponentials;
+  out->matvecs = st->matvecs;
+  out->min_m_eff = st->min_m_eff;
+  out->breakdowns = st->breakdowns;
+  out->last_norm2 = st->last_norm2;
+  for (int q = 0; q < 4; ++q) out->seg[q] = st->seg[q];
+  const int status =
+      __hip_atomic_load(&st->status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (status != CFET_OK)
+    __hip_atomic_store(&out->status, status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // The work of one block.  NF: terms of a set that leave the block, at most (0:
 // one block); CS: cache policy of the stores that other blocks read.
 template <int T, int R, int MODE, int NF, bool RV, int CS>
@@ -715,13 +744,9 @@ __device__ __forceinline__ void site_run(const SiteArgs& A, int rank, double2* x
     }
     if (tm.on)
       for (int q = 0; q < 4; ++q) st->seg[q] += tm.acc[q];
-    if (A.p.stats_out) *A.p.stats_out = *st;
+    publish_stats(A);
   }
-  if (!ok && t == 0) {
-    __hip_atomic_store(&A.p.stats->status, (int)CFET_EDEVICE, __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
-    if (A.p.stats_out) A.p.stats_out->status = (int)CFET_EDEVICE;
-  }
+  if (!ok && t == 0) report_fault(A);
 }
 
 template <int T, int R, int MODE, bool RV>
@@ -761,7 +786,7 @@ __global__ __launch_bounds__(T) void k_site_team(SiteArgs A) {
     unsigned long long v;
     for (int spin = 0;; ++spin) {
       v = __hip_atomic_load(A.ids + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if ((v >> 4) == sh.launch) break;
+      if ((v >> 4) == sh.launch + A.skew) break;
       if ((spin & 15) == 15 && wall_clock64() - t0 > A.p.spin_limit) {
         sh.bad = 1;
         break;
@@ -772,13 +797,11 @@ __global__ __launch_bounds__(T) void k_site_team(SiteArgs A) {
   }
   __syncthreads();
   if (sh.bad) {
-    if (t == 0)
-      __hip_atomic_store(&A.p.stats->status, (int)CFET_EDEVICE, __ATOMIC_RELAXED,
-                         __HIP_MEMORY_SCOPE_AGENT);
+    if (t == 0) report_fault(A);
     return;
   }
   int team = -1;
-  for (int x = 15; x >= 0; --x)
+  for (int x = 15; x >= 0 && !A.spread; --x)
     if (sh.hist[x] >= A.blocks) team = x;
   if (team >= 0) {
     if ((int)xcc == team && sh.rank < A.blocks) 
@@ -965,6 +988,8 @@ hipError_t launch_site(const DevSite& S, const PersistArgs& args, hipStream_t st
   A.rec = S.rec;
   A.ids = S.ids;
   A.count = S.count;
+  A.skew = S.skew;
+  A.spread = S.spread;
   const void* fn = site_shape(S.plan, S.real).fn;
   void* kargs[] = {&A};
   if (S.plan.blocks == 1)

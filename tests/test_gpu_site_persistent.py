@@ -210,3 +210,19 @@ def test_two_streams_and_two_contexts():
     for (P, psi0, ref, s), psi in zip(jobs, outs):
         assert P.stats()["status"] == 0 and torch.equal(psi, ref)
         P.close()
+
+
+def test_a_team_that_does_not_form_is_reported():
+    H0, Hk, drives, psi0 = chain("ising", 12, 5)
+    with B.Propagator(H0, Hk, drives, test="no_team") as P:
+        psi = dev(psi0)
+        P.propagate(psi, 0.0, 0.05, 2, "CF4:2", 12)
+        torch.cuda.synchronize()
+        assert np.array_equal(psi.cpu().numpy(), psi0)
+        with pytest.raises(B.CfetError) as e:       # the next call reports it
+            P.propagate(psi, 0.0, 0.05, 2, "CF4:2", 12)
+        assert B.ERRORS[e.value.code] == "CFET_EDEVICE"
+        with pytest.raises(B.CfetError) as e:       # and so does a run that waits
+            P.select_dt(psi, 0.0, 0.1, 2, "CF4:2", 12, 1.0, 1e-6)
+        assert B.ERRORS[e.value.code] == "CFET_EDEVICE"
+        assert P.stats()["status"] == e.value.code
