@@ -226,3 +226,39 @@ def test_a_team_that_does_not_form_is_reported():
             P.select_dt(psi, 0.0, 0.1, 2, "CF4:2", 12, 1.0, 1e-6)
         assert B.ERRORS[e.value.code] == "CFET_EDEVICE"
         assert P.stats()["status"] == e.value.code
+
+
+@pytest.mark.parametrize("model,L", [("ising", 11), ("heisenberg", 12), ("spins", 12),
+                                     ("y", 13), ("driven_diag", 13), ("ising", 14)])
+def test_a_team_spread_over_the_xcds_gives_the_same_bits(model, L):
+    # the exchange with device-scope stores, taken where no XCD holds a team
+    H0, Hk, drives, psi0 = chain(model, L, 7 * L)
+    rng = np.random.default_rng(L)
+    n, N, dt = 1 << L, 6, 0.04
+    pwc = [{"kind": "pwc", "t_edges": np.linspace(0.0, N * dt, 4), "u": rng.uniform(-1, 1, 3)}]
+    target = I.random_state(n, rng)
+    plus = np.full(n, 2.0 ** (-L / 2), dtype=complex)
+    got = []
+    for test in (None, "spread_team"):
+        with B.Propagator(H0, Hk, drives, test=test) as P:
+            psi = dev(psi0)
+            P.propagate(psi, 0.1, dt, N, "CF6:5Opt", 14)
+            zero = dev(np.zeros(n))
+            P.propagate(zero, 0.1, dt, 1, "CF4:2", 14)
+            st = P.stats()
+            assert st["status"] == 0 and B.PATH_NAMES[st["path"]] == "coop"
+            got.append([psi.cpu().numpy(), zero.cpu().numpy(), st["matvecs"], st["last_norm"]])
+        # a recurrence that stops early
+        with B.Propagator(I.diagonal(np.full(n, 0.7)), [I.sigma_x_sum(L)],
+                          [dict(drives[0], omega=0.0)], test=test) as P:
+            psi = dev(plus)
+            P.propagate(psi, 0.0, 0.2, 2, "CF4:2", 10)
+            st = P.stats()
+            assert st["status"] == 0 and st["breakdowns"] == 4
+            got[-1].append(psi.cpu().numpy())
+        if len(Hk) == 1:
+            with B.Propagator(H0, Hk, pwc, test=test) as P:
+                got[-1] += P.gradient(dev(psi0), dev(target), 0.0, dt, N, "CF4:2", 14)
+                assert P.stats()["status"] == 0
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
