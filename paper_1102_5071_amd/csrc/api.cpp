@@ -97,12 +97,37 @@ thread_local std::string g_err;
 // automatic path choice by dimension
 constexpr int64_t kAutoSingleMaxN = 4096;
 constexpr int64_t kAutoCoopMaxN = int64_t(1) << 22;
-// smallest dimension of the sweeps on the site-operator form
+// Smallest dimension of the sweeps on the site-operator form, and the fewest
+// stored entries: two launches an iteration cost 11 to 14 us at 2^16 to 2^18 rows
+// whatever the operator, so an operator of few entries stays on the CSR kernels.
+// (2^18 rows, four steps of two exponentials with 14 vectors, CSR and sweeps: one
+// driven site, 0.5 M entries, 1606 and 1744 us; three, 1.0 M, 1964 and 1763; a
+// Chebyshev run 568 and 803, 747 and 712.)
 constexpr int64_t kParityMinN = int64_t(1) << 16;
+constexpr int64_t kParityMinNnz = int64_t(1) << 20;
+// ... and where the cooperative kernel holds the rows in registers, up to this
+// many entries of the longest row, it serves the operator: 2^16 rows with 16
+// entries 702 us (the same run), the sweeps 1304; with 17, of which its block
+// shape then holds five, 1634 and 1345.  2^17 rows: 8 entries 690 and 1586, 9
+// (five held) 1312 and 1591, 11 1729 and 1458.
+constexpr int kParityCoopTail = 4;
 // Grid of the cooperative kernel: one block per CU, but at least ~128 rows per
 // block; each block owns ceil(n / blocks) consecutive rows.
 int64_t coop_grid_blocks(int64_t n, int cus) {
   return std::max<int64_t>(1, std::min<int64_t>(cus, (n + 127) / 128));
+}
+// True if the cooperative kernel runs an operator of this longest row with at
+// most kParityCoopTail of its entries outside registers.
+bool coop_serves(int64_t n, int nterms, int max_row, bool real, int device) {
+  if (n > kAutoCoopMaxN) return false;
+  int cus = 0, most = 0;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess ||
+      cus <= 0)
+    return false;
+  const int64_t blocks = coop_grid_blocks(n, cus);
+  const int p = cfet::persistent_choose_preset(max_row, (n + blocks - 1) / blocks, false);
+  return p >= 0 && max_row <= cfet::persistent_row_entries(p, false) + kParityCoopTail &&
+         cfet::persistent_max_blocks(p, nterms, real, &most) == hipSuccess && most >= blocks;
 }
 
 // device bytes the gradient may spend on keeping the recomputed projections
@@ -1485,7 +1510,9 @@ int cfet_create(const cfet_csr* H0, int32_t nterms, const cfet_csr* Hk, const cf
         c->site.spread = (flags & CFET_TEST_SPREAD_TEAM) ? 1 : 0;
       }
     }
-    if (found && n >= kParityMinN && cfet::plan_parity(form, &c->parity.plan)) {
+    if (found && n >= kParityMinN && nnz >= kParityMinNnz &&
+        !coop_serves(n, nterms, c->max_row, form.real, c->device) &&
+        cfet::plan_parity(form, &c->parity.plan)) {
       c->parity.ok = true;
       c->parity.real = form.real;
       c->parity.diag_term = form.diag_term;

@@ -363,6 +363,7 @@ hipError_t launch_persistent(const PersistArgs& args, int preset, bool single, i
 // real: occupancy of the real-valued form (the one launched for real operators)
 hipError_t persistent_max_blocks(int preset, int nterms, bool real, int* out);
 int persistent_rows_per_block(int preset, bool single);
+int persistent_row_entries(int preset, bool single);  // entries of a row that it holds in registers
 int persistent_block_threads(int preset, bool single);
 int persistent_barrier_words();
 int persistent_choose_preset(int max_row, int64_t min_rows_per_block, bool single);

@@ -881,6 +881,12 @@ int persistent_rows_per_block(int preset, bool single) {
   return single ? std::min(rows, kSingleMaxRows) : rows;
 }
 
+int persistent_row_entries(int preset, bool single) {
+  const Preset* t = single ? kSinglePresets : kCoopPresets;
+  const int np = single ? kNumSinglePresets : kNumCoopPresets;
+  return (preset < 0 || preset >= np) ? 0 : t[preset].G * t[preset].Q;
+}
+
 // Preset for a matrix: prefer one that holds the longest row in registers,
 // then the one holding the fewest entries per lane (register pressure), among
 // those whose block capacity is at least min_rows_per_block.

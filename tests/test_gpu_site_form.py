@@ -244,3 +244,36 @@ def test_static_and_streams_and_repeat():
         P.propagate_static(c, 0.0, 0.05, 1, "CF4:2", 12)
         torch.cuda.synchronize()
         assert torch.equal(a, b) and torch.equal(a, c)
+
+
+def driven_sites(L, k):
+    """sigma^x on the k highest sites."""
+    X = I.sigma_x_sum(L)
+    return I.CSR(X.n, np.arange(X.n + 1, dtype=np.int64) * k,
+                 X.col.reshape(-1, L)[:, L - k:].ravel(), X.val.reshape(-1, L)[:, L - k:].ravel())
+
+
+@pytest.mark.parametrize("L,k,route", [
+    (16, 2, "coop"), (16, 15, "coop"), (16, 16, "sweeps"),
+    (17, 7, "coop"), (17, 8, "coop"), (17, 10, "sweeps"),
+    (18, 1, "csr"), (18, 2, "csr"), (18, 3, "sweeps")])
+def test_few_driven_sites_keep_the_csr_kernels(L, k, route):
+    # 1 + k entries per row: rows that the cooperative kernel holds (16 at 2^16, 8
+    # and one more at 2^17), or fewer than 2^20 entries
+    rng = np.random.default_rng(L + k)
+    H0, H1 = I.ising_chain(L, 1.0, rng.uniform(-1, 1, L)), driven_sites(L, k)
+    psi0 = I.random_product_state(L, rng)
+    with B.Propagator(H0, [H1], COS[:1]) as P:
+        x = dev(psi0)
+        y = P.apply(x, 0.9, [-0.4]).cpu().numpy()
+        psi, che = x.clone(), x.clone()
+        P.propagate(psi, 0.1, 0.02, 1, "CF4:2", 12)
+        st = P.stats()
+        P.propagate_chebyshev(che, 0.1, 0.02, 1, "CF4:2", 1e-12)
+        assert P.stats()["status"] == 0
+    assert B.PATH_NAMES[st["path"]] == ("coop" if route == "coop" else "multi")
+    assert (st["matrix_bytes"] < 16 << L) == (route == "sweeps")
+    ref = O.propagate(H0, [H1], COS[:1], psi0, 0.1, 0.02, 1, "CF4:2", m=12)
+    assert rel(y, 0.9 * (H0.to_scipy() @ psi0) - 0.4 * (H1.to_scipy() @ psi0)) < 1e-14
+    assert rel(psi.cpu().numpy(), ref) <= 1e-10
+    assert rel(che.cpu().numpy(), ref) <= 1e-10
