@@ -111,6 +111,10 @@ constexpr int64_t kParityMinNnz = int64_t(1) << 20;
 // shape then holds five, 1634 and 1345.  2^17 rows: 8 entries 690 and 1586, 9
 // (five held) 1312 and 1591, 11 1729 and 1458.
 constexpr int kParityCoopTail = 4;
+// Stored entries from which one product alone (cfet_apply) takes the sweeps: two
+// launches against one.  (Back to back, CSR and sweeps: 2^16 rows, 1.1 M entries 9.7
+// and 12.5 us, 2.2 M 11.9 and 12.7; 2^17 rows, 1.4 M 9.5 and 12, 2.4 M 13.3 and 12.3.)
+constexpr int64_t kParityApplyNnz = int64_t(9) << 18;
 // Grid of the cooperative kernel: one block per CU, but at least ~128 rows per
 // block; each block owns ceil(n / blocks) consecutive rows.
 int64_t coop_grid_blocks(int64_t n, int cus) {
@@ -1981,7 +1985,7 @@ int cfet_apply(cfet_ctx* c, const void* x_dev, void* y_dev, double a, const doub
   for (int k = 0; k < c->nterms; ++k) tw.w[k + 1] = b[k];
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   hipError_t e;
-  if (c->parity.ok) {
+  if (c->parity.ok && (!c->A.rowptr || c->A.nnz >= kParityApplyNnz)) {
     e = cfet::launch_parity_apply(c->parity, tw, static_cast<const double2*>(x_dev),
                                   static_cast<double2*>(y_dev), cfet::ChebTerm{}, st);
   } else if (c->use_sell && c->hi.nuni) {

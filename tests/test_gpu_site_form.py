@@ -277,3 +277,36 @@ def test_few_driven_sites_keep_the_csr_kernels(L, k, route):
     assert rel(y, 0.9 * (H0.to_scipy() @ psi0) - 0.4 * (H1.to_scipy() @ psi0)) < 1e-14
     assert rel(psi.cpu().numpy(), ref) <= 1e-10
     assert rel(che.cpu().numpy(), ref) <= 1e-10
+
+
+@pytest.mark.parametrize("model,L,form", [("ising", 16, False), ("heisenberg", 16, False),
+                                          ("ising", 17, True)])
+def test_one_product_of_few_entries_runs_on_the_csr_kernel(model, L, form):
+    # below 9 * 2^18 entries: the same bits as on the multi-kernel CSR path
+    rng = np.random.default_rng(L)
+    h = rng.uniform(-1, 1, L)
+    H0 = (I.heisenberg_chain if model == "heisenberg" else I.ising_chain)(L, 1.0, h)
+    H1, x = I.sigma_x_sum(L), I.random_state(1 << L, rng)
+    got = []
+    for path in (None, "multi"):
+        with B.Propagator(H0, [H1], COS[:1], path=path, reorder=False) as P:
+            got.append(P.apply(dev(x), 0.9, [-0.4]).cpu().numpy())
+    assert rel(got[0], got[1]) < 1e-14
+    assert np.array_equal(got[0], got[1]) == (not form)
+
+
+def test_few_entries_where_no_csr_is_kept():
+    # 2^23 rows, a diagonal on every sixth of them: the sweeps, whatever the count
+    n = 1 << 23
+    at = np.arange(0, n, 6)
+    rp = np.zeros(n + 1, np.int64)
+    rp[at + 1] = 1
+    d = np.random.default_rng(2).uniform(-1, 1, at.size)
+    H0 = I.CSR(n, np.cumsum(rp), at.astype(np.int32), d.astype(complex))
+    H1 = I.CSR(n, np.zeros(n + 1, np.int64), np.zeros(0, np.int32), np.zeros(0, complex))
+    x = I.random_state(n, np.random.default_rng(3))
+    with B.Propagator(H0, [H1], COS[:1]) as P:
+        y = P.apply(dev(x), 1.7, [0.3]).cpu().numpy()
+    ref = np.zeros(n, complex)
+    ref[at] = 1.7 * d * x[at]
+    assert rel(y, ref) < 1e-14
