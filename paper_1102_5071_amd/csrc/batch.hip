@@ -228,7 +228,7 @@ constexpr int kFlipT = 512;
 constexpr int kFlipR = (1 << kFlipBits) / kFlipT;
 
 template <bool HI>
-__device__ __forceinline__ int flip_group(const BGroup* G, int ng, int b) {
+__device__ __forceinline__ int flip_group(const BFlip* G, int ng, int b) {
   int lo = 0, hi = ng - 1;
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
@@ -256,12 +256,13 @@ __device__ __forceinline__ void flip_registers(double2 (&acc)[kFlipR], const dou
 
 __global__ __launch_bounds__(kFlipT, 4) void k_b_high(BLaunch L, int k) {
   __shared__ double2 xt[1 << kFlipBits];
-  const int g = flip_group<true>(L.groups, L.ngroups, blockIdx.x);
+  const int g = flip_group<true>(L.flips, L.ngroups, blockIdx.x);
   const BGroup gr = L.groups[g];
+  const BFlip fl = L.flips[g];
   if (group_idle(gr, L.S.done)) return;
   const int t = threadIdx.x;
-  const int low = 2 * kFlipBits - gr.nv;
-  const uint32_t tile = (uint32_t)(blockIdx.x - gr.hblock0) << low;
+  const int low = 2 * kFlipBits - fl.nv;
+  const uint32_t tile = (uint32_t)(blockIdx.x - fl.hblock0) << low;
   const double2* __restrict__ x = L.V + (int64_t)k * L.ntot + gr.voff;
   double2* __restrict__ y = L.Y + gr.voff;
   uint32_t idx[kFlipR];
@@ -276,7 +277,7 @@ __global__ __launch_bounds__(kFlipT, 4) void k_b_high(BLaunch L, int k) {
 #pragma unroll
   for (int r = 0; r < kFlipR; ++r) xt[t + r * kFlipT] = xo[r];
   __syncthreads();
-  const double* __restrict__ c = gr.coef + kFlipBits - low;  // by tile bit
+  const double* __restrict__ c = fl.coef + kFlipBits - low;  // by tile bit
   flip_registers(acc, xo, c + kFlipBits - 3);
   for (int p = low; p < kFlipBits - 3; ++p) {
     const double cp = c[p];
@@ -289,13 +290,14 @@ __global__ __launch_bounds__(kFlipT, 4) void k_b_high(BLaunch L, int k) {
 
 __global__ __launch_bounds__(kFlipT, 4) void k_b_low(BLaunch L, int k) {
   __shared__ double2 xt[1 << kFlipBits];
-  const int g = flip_group<false>(L.groups, L.ngroups, blockIdx.x);
+  const int g = flip_group<false>(L.flips, L.ngroups, blockIdx.x);
   const BGroup gr = L.groups[g];
+  const BFlip fl = L.flips[g];
   if (group_idle(gr, L.S.done)) return;
   const int t = threadIdx.x;
-  const int tile = blockIdx.x - gr.sblock0;
+  const int tile = blockIdx.x - fl.sblock0;
   const uint32_t e0 = (uint32_t)tile << kFlipBits;
-  const uint32_t ne = 1u << gr.nv;
+  const uint32_t ne = 1u << fl.nv;
   const BState* st = L.st;
   const int slot = gr.slot0 + (t & (gr.B - 1));
   const bool act = L.S.done[slot] == 0;
@@ -312,16 +314,16 @@ __global__ __launch_bounds__(kFlipT, 4) void k_b_low(BLaunch L, int k) {
     const uint32_t i = e0 + (uint32_t)(t + r * kFlipT);
     const bool in = act && i < ne;  // (lanes of an instance only read their own)
     xo[r] = in ? x[i] : make_double2(0.0, 0.0);
-    acc[r] = (in && gr.hblocks) ? y[i] : make_double2(0.0, 0.0);
-    d[r] = in ? __builtin_nontemporal_load(gr.diagr + i) : 0.0;
+    acc[r] = (in && fl.hblocks) ? y[i] : make_double2(0.0, 0.0);
+    d[r] = in ? __builtin_nontemporal_load(fl.diagr + i) : 0.0;
   }
 #pragma unroll
   for (int r = 0; r < kFlipR; ++r) xt[t + r * kFlipT] = xo[r];
   __syncthreads();
-  const double* __restrict__ c = gr.coef;
+  const double* __restrict__ c = fl.coef;
   flip_registers(acc, xo, c + kFlipBits - 3);
-  if (!gr.hblocks)
-    for (int v = kFlipBits; v < gr.nv; ++v) {
+  if (!fl.hblocks)
+    for (int v = kFlipBits; v < fl.nv; ++v) {
       const double cv = c[v];
 #pragma unroll
       for (int r = 0; r < kFlipR; ++r)
@@ -496,8 +498,8 @@ __global__ __launch_bounds__(64) void k_b_scalars(BLaunch L, int mode, int k) {
   }
   if (L.S.done[slot]) return;
   const int mcap = L.S.mcap[slot];
-  if (mode == kBAlpha) {
-    const double a = slot_sum(L, gr, j, L.low_blocks ? gr.sblocks : gr.nblocks);
+  if (mode == kBAlpha || mode == kBAlphaFlip) {
+    const double a = slot_sum(L, gr, j, mode == kBAlphaFlip ? L.flips[g].sblocks : gr.nblocks);
     if (lane == 0) L.S.alpha[sb + k] = a;
     wave_sync();
     if (k == mcap - 1) finish_slot(L, slot, k + 1, dt, lds, false, make_double2(0.0, 0.0), 0);
@@ -592,12 +594,13 @@ hipError_t batch_norm(const BLaunch& L, hipStream_t s) {
 }
 
 hipError_t batch_scalars(const BLaunch& L, int mode, int k, hipStream_t s) {
+  if (mode == kBAlpha && L.flips) mode = kBAlphaFlip;
   hipLaunchKernelGGL(k_b_scalars, dim3(L.nslots), dim3(64), 0, s, L, mode, k);
   return hipGetLastError();
 }
 
 hipError_t batch_spmm(const BLaunch& L, int k, hipStream_t s) {
-  if (L.low_blocks) {
+  if (L.flips) {
     if (L.high_blocks)
       hipLaunchKernelGGL(k_b_high, dim3(L.high_blocks), dim3(kFlipT), 0, s, L, k);
     hipLaunchKernelGGL(k_b_low, dim3(L.low_blocks), dim3(kFlipT), 0, s, L, k);

@@ -38,10 +38,12 @@ struct cfet_batch {
   std::vector<std::vector<DriveSpec>> drives;  // per slot
   std::vector<BGroup> groups;
   BGroup* d_groups = nullptr;
+  std::vector<cfet::BFlip> flips;  // by group (empty: k_b_spmm)
+  cfet::BFlip* d_flips = nullptr;
   std::vector<void*> allocs;       // operator arrays
   int64_t ntot = 0;
   int total_blocks = 0;
-  int low_blocks = 0, high_blocks = 0;  // flip sweeps (0: k_b_spmm)
+  int low_blocks = 0, high_blocks = 0;  // flip sweeps
   int64_t pstride = 0;             // partial sums per instance (most blocks of a group)
   int unroll = 1;                  // rows per lane and pass (autotuned)
   int waves = cfet::kBatchDefaultWaves;  // wavefronts per block of the row kernels (autotuned)
@@ -103,7 +105,7 @@ void free_batch(cfet_batch* b) {
   if (b->exec) (void)hipGraphExecDestroy(b->exec);
   if (b->cap_stream) (void)hipStreamDestroy(b->cap_stream);
   for (void* p : b->allocs) (void)hipFree(p);
-  void* dev[] = {b->d_groups, b->V, b->Y, b->part, b->st, b->d_uoff, b->d_wts,
+  void* dev[] = {b->d_groups, b->d_flips, b->V, b->Y, b->part, b->st, b->d_uoff, b->d_wts,
                  b->S.alpha, b->S.beta, b->S.inv, b->S.coef, b->S.beta0, b->S.m_eff,
                  b->S.done, b->S.mcap, b->S.matvecs, b->S.expos, b->S.breakdowns,
                  b->S.early, b->S.min_m, b->S.max_m};
@@ -172,6 +174,7 @@ BLaunch launch_of(const cfet_batch* b) {
   L.Y = b->Y;
   L.part = b->part;
   L.pstride = b->pstride;
+  L.flips = b->d_flips;
   L.low_blocks = b->low_blocks;
   L.high_blocks = b->high_blocks;
   L.waves = b->waves;
@@ -564,8 +567,9 @@ CFET_API int cfet_batch_create(int32_t nops, const cfet_csr* ops, int32_t ninst,
         // factors by element bit, real diagonal, tiles
         int lb = 0;
         while ((1 << lb) < B) ++lb;
-        g.nv = lb;
-        while ((int64_t(1) << (g.nv - lb)) < n) ++g.nv;
+        cfet::BFlip fl{};
+        fl.nv = lb;
+        while ((int64_t(1) << (fl.nv - lb)) < n) ++fl.nv;
         std::vector<double> cf(24, 0.0), dr(diag.size() / 2);
         const std::vector<double>& f = flip_of[key];
         for (size_t i = 0; i < f.size(); ++i) cf[i + size_t(lb)] = f[i];
@@ -579,10 +583,11 @@ CFET_API int cfet_batch_create(int32_t nops, const cfet_csr* ops, int32_t ninst,
           e = hipMemcpy(dc, cf.data(), cf.size() * sizeof(double), hipMemcpyHostToDevice);
         if (e == hipSuccess)
           e = hipMemcpy(dv, dr.data(), dr.size() * sizeof(double), hipMemcpyHostToDevice);
-        g.coef = dc;
-        g.diagr = dv;
-        g.sblocks = std::max(1, 1 << std::max(0, g.nv - cfet::kFlipBits));
-        g.hblocks = g.nv - cfet::kFlipBits > cfet::kFlipGather ? g.sblocks : 0;
+        fl.coef = dc;
+        fl.diagr = dv;
+        fl.sblocks = 1 << std::max(0, fl.nv - cfet::kFlipBits);
+        fl.hblocks = fl.nv - cfet::kFlipBits > cfet::kFlipGather ? fl.sblocks : 0;
+        b->flips.push_back(fl);
       }
       if (e == hipSuccess && any_off) {
         int64_t* drp = nullptr;
@@ -615,12 +620,12 @@ CFET_API int cfet_batch_create(int32_t nops, const cfet_csr* ops, int32_t ninst,
     free_batch(b);
     return rc;
   }
-  for (auto& g : b->groups) {  // (no tiles without the flip sweeps)
-    g.sblock0 = b->low_blocks;
-    g.hblock0 = b->high_blocks;
-    b->low_blocks += g.sblocks;
-    b->high_blocks += g.hblocks;
-    b->pstride = std::max<int64_t>(b->pstride, g.sblocks);
+  for (auto& f : b->flips) {
+    f.sblock0 = b->low_blocks;
+    f.hblock0 = b->high_blocks;
+    b->low_blocks += f.sblocks;
+    b->high_blocks += f.hblocks;
+    b->pstride = std::max<int64_t>(b->pstride, f.sblocks);
   }
   b->ntot = voff;
   // partial-sum rows sized for the layout with the most blocks (the smallest
@@ -630,6 +635,12 @@ CFET_API int cfet_batch_create(int32_t nops, const cfet_csr* ops, int32_t ninst,
   // per-slot state and workspace
   const size_t ns = size_t(ninst), nm = ns * cfet::kMaxM;
   e = dalloc(&b->d_groups, b->groups.size());
+  if (e == hipSuccess && !b->flips.empty()) {
+    e = dalloc(&b->d_flips, b->flips.size());
+    if (e == hipSuccess)
+      e = hipMemcpy(b->d_flips, b->flips.data(), b->flips.size() * sizeof(cfet::BFlip),
+                    hipMemcpyHostToDevice);
+  }
   if (e == hipSuccess) e = dalloc(&b->Y, size_t(b->ntot));
   if (e == hipSuccess) e = dalloc(&b->part, size_t(ninst) * size_t(b->pstride));
   if (e == hipSuccess) e = dalloc(&b->st, 1);

@@ -46,12 +46,7 @@ struct BGroup {
   int block0;           // first block of the group in that grid
   int slot0;            // first instance slot of the group
   int shared_h0;        // 1: H0 is term 0 of the shared operator
-  int nv;               // flip sweeps: n * B = 2^nv elements,
-  int sblocks, sblock0; //   tiles of the low sweep (all groups) and
-  int hblocks, hblock0; //   of the high sweep (0: the low sweep gathers)
   int pad;
-  const double* coef;   // flip sweeps: factor of the flip of element bit v < 24
-  const double* diagr;  // flip sweeps: [n][B] real H0 diagonal
   const int64_t* rowptr;  // shared operator, n + 1 row pointers
   const uint32_t* colt;   // column | term << kTermShift
   const double2* val;
@@ -59,6 +54,17 @@ struct BGroup {
   const int64_t* orp;     // [B][n + 1] H0 off-diagonal rows per instance, or null
   const int32_t* ocol;
   const double2* oval;
+};
+
+// What the flip sweeps read of a group besides (an array of its own: the row
+// kernels load a BGroup in every block).
+struct BFlip {
+  int nv;               // n * B = 2^nv elements
+  int sblocks, sblock0; // tiles of the low sweep (all groups) and
+  int hblocks, hblock0; // of the high sweep (0: the low sweep gathers)
+  int pad;
+  const double* coef;   // factor of the flip of element bit v < 24
+  const double* diagr;  // [n][B] real H0 diagonal
 };
 
 // Per-slot Lanczos state and statistics (slot = instance in group order).
@@ -102,14 +108,16 @@ struct BLaunch {
   double2* Y;            // H v_k
   double* part;          // [slot][pstride] partial sums: instance slot, block of its group
   int64_t pstride;
-  int low_blocks;        // flip sweeps: blocks of the low sweep (0: k_b_spmm) and
-  int high_blocks;       //   of the high sweep
   int waves;             // wavefronts per block of the row kernels (2, 4 or 8)
   BSlots S;
   BState* st;
+  const BFlip* flips;    // flip sweeps, by group (null: k_b_spmm), and
+  int low_blocks;        //   blocks of the low sweep
+  int high_blocks;       //   and of the high sweep
 };
 
-enum BScalarMode { kBStart = 0, kBAlpha = 1, kBBeta = 2 };
+// (kBAlphaFlip: the partials of the low sweep's tiles)
+enum BScalarMode { kBStart = 0, kBAlpha = 1, kBBeta = 2, kBAlphaFlip = 3 };
 
 hipError_t batch_norm(const BLaunch& L, hipStream_t s);
 hipError_t batch_scalars(const BLaunch& L, int mode, int k, hipStream_t s);
