@@ -103,7 +103,7 @@ constexpr int64_t kAutoCoopMaxN = int64_t(1) << 22;
 // (2^18 rows, four steps of two exponentials with 14 vectors, CSR and sweeps: one
 // driven site, 0.5 M entries, 1606 and 1744 us; three, 1.0 M, 1964 and 1763; a
 // Chebyshev run 568 and 803, 747 and 712.)
-constexpr int64_t kParityMinN = int64_t(1) << 16;
+constexpr int64_t kParityMinN = int64_t(1) << cfet::kParityMinBits;
 constexpr int64_t kParityMinNnz = int64_t(1) << 20;
 // ... and where the cooperative kernel holds the rows in registers, up to this
 // many entries of the longest row, it serves the operator: 2^16 rows with 16

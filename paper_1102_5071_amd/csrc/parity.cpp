@@ -261,7 +261,7 @@ void tiles_of(int nb, int* tbh, int* tbl, int* low) {
     *tbh = *tbl = 12;
     *low = nb >= 25 ? 3 : 4;
   } else {
-    *tbh = nb >= 19 ? 11 : nb >= 17 ? 10 : nb >= 15 ? 9 : 8;
+    *tbh = nb >= 19 ? 11 : nb >= 17 ? 10 : 9;
     *tbl = nb == 21 ? 12 : *tbh;
     *low = nb == 22 ? 3 : 2;
   }

@@ -63,7 +63,7 @@ struct ParityPlan {
   int low = 0, high = 0;           // tbh = low + nb - high
   std::vector<ParityTerm> hi, lo, far;
 };
-constexpr int kParityMinBits = 14;
+constexpr int kParityMinBits = 16;
 constexpr int kParityMaxBits = 27;  // byte offsets inside a vector fit 32 bits
 bool plan_parity(const ParityForm& F, ParityPlan* P);
 

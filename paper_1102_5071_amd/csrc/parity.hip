@@ -188,7 +188,7 @@ struct WElem {
 constexpr int batch_of(int R) { return R <= 2 ? 4 : R == 4 ? 2 : 1; }
 
 template <int TB, int T, bool RV, bool HI, int OP, bool NTL>
-__global__ __launch_bounds__(T, RV || T > 512 ? 4 : 2) void k_sweep(SweepArgs A) {
+__global__ __launch_bounds__(T, RV ? 4 : 2) void k_sweep(SweepArgs A) {
   constexpr int R = (1 << TB) / T;
   constexpr int CH = R < 4 ? R : 4;  // rows whose tile reads are in flight together
   constexpr int U = batch_of(R);     // and terms
@@ -496,7 +496,7 @@ __global__ __launch_bounds__(64) void k_parity_small(const double2* part, int np
   }
 }
 
-constexpr int threads_of(int tb) { return tb >= 13 ? 1024 : tb >= 10 ? 512 : tb == 9 ? 256 : 128; }
+constexpr int threads_of(int tb) { return tb >= 10 ? 512 : 256; }
 
 size_t lds_of(int tb) {
   return (size_t(16) << tb) + kSweepTerms * sizeof(WElem) +
@@ -512,27 +512,22 @@ void go(const SweepArgs& A, hipStream_t st) {
 // Non-temporal accesses of the vectors that stream through, where a vector
 // does not fit the memory-side cache (256 MB); below that they evict what the
 // next launch reads (2^20 rows: 39.6 us per iteration with them, 35.8 without;
-// 2^22: equal).
+// 2^22: equal).  Such vectors take the largest tile.
 constexpr int kStreamBits = 24;
 
 template <bool RV, bool HI, int OP>
 hipError_t go_tb(const SweepArgs& A, hipStream_t st) {
-  const bool stream = A.nb >= kStreamBits;
-#define CFET_TILE(B)                                  \
-  case B:                                             \
-    if (stream) go<B, RV, HI, OP, true>(A, st);       \
-    else go<B, RV, HI, OP, false>(A, st);             \
-    break;
+  if (A.nb >= kStreamBits && A.tb != 12) return hipErrorInvalidValue;
   switch (A.tb) {
-    CFET_TILE(8)
-    CFET_TILE(9)
-    CFET_TILE(10)
-    CFET_TILE(11)
-    CFET_TILE(12)
-    CFET_TILE(13)
+    case 9: go<9, RV, HI, OP, false>(A, st); break;
+    case 10: go<10, RV, HI, OP, false>(A, st); break;
+    case 11: go<11, RV, HI, OP, false>(A, st); break;
+    case 12:
+      if (A.nb >= kStreamBits) go<12, RV, HI, OP, true>(A, st);
+      else go<12, RV, HI, OP, false>(A, st);
+      break;
     default: return hipErrorInvalidValue;
   }
-#undef CFET_TILE
   return hipGetLastError();
 }
 
@@ -563,9 +558,9 @@ hipError_t allow(K kernel, size_t bytes) {
                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
-template <int TB, bool RV, bool HI, bool NTL>
+template <bool RV, bool HI, bool NTL>
 hipError_t allow_ops() {
-  constexpr int T = threads_of(TB);
+  constexpr int TB = 12, T = threads_of(TB);
   const size_t b = lds_of(TB);
   hipError_t e = allow(k_sweep<TB, T, RV, HI, kApply, NTL>, b);
   if (e == hipSuccess) e = allow(k_sweep<TB, T, RV, HI, kLanczos, NTL>, b);
@@ -574,16 +569,12 @@ hipError_t allow_ops() {
   return e;
 }
 
-template <int TB>
-hipError_t allow_tile() {
-  hipError_t e = allow_ops<TB, true, true, true>();
-  if (e == hipSuccess) e = allow_ops<TB, true, false, true>();
-  if (e == hipSuccess) e = allow_ops<TB, false, true, true>();
-  if (e == hipSuccess) e = allow_ops<TB, false, false, true>();
-  if (e == hipSuccess) e = allow_ops<TB, true, true, false>();
-  if (e == hipSuccess) e = allow_ops<TB, true, false, false>();
-  if (e == hipSuccess) e = allow_ops<TB, false, true, false>();
-  if (e == hipSuccess) e = allow_ops<TB, false, false, false>();
+template <bool RV>
+hipError_t allow_values() {
+  hipError_t e = allow_ops<RV, true, true>();
+  if (e == hipSuccess) e = allow_ops<RV, false, true>();
+  if (e == hipSuccess) e = allow_ops<RV, true, false>();
+  if (e == hipSuccess) e = allow_ops<RV, false, false>();
   return e;
 }
 
@@ -596,9 +587,8 @@ int parity_grid(const ParityPlan& P, int num_cus) {
 
 // Allows the kernels on the largest tile their LDS (above 64 KiB).
 hipError_t parity_prepare() {
-  hipError_t e = allow_tile<12>();
-  if (e == hipSuccess) e = allow_tile<13>();
-  return e;
+  const hipError_t e = allow_values<true>();
+  return e == hipSuccess ? allow_values<false>() : e;
 }
 
 void parity_tables(const ParityPlan& P, PElem* out, int n[2][5]) {
