@@ -179,7 +179,8 @@ __device__ __forceinline__ void st(double2* p, double2 v) {
 // register index alone (their x is in this thread's registers); n[4] terms
 // gathered from memory (second sweep).
 struct WElem {
-  uint32_t off, pmask, rpar, pad;
+  uint32_t off, pmask, rpar;
+  uint32_t has;  // bit p: the operator stores an entry on rows of parity p
   double v0, v1;
   double w0, w1;
 };
@@ -195,6 +196,13 @@ __global__ __launch_bounds__(T, RV ? 4 : 2) void k_sweep(SweepArgs A) {
   extern __shared__ double2 xt[];
   WElem* we = reinterpret_cast<WElem*>(xt + (1 << TB));
   double* red = reinterpret_cast<double*>(we + kSweepTerms);
+  // by wavefront: its part of the tile holds an infinity or a NaN
+  volatile uint8_t* odd_x = reinterpret_cast<uint8_t*>(red + 2 * (T / 64));
+  auto any_odd = [&]() {
+    unsigned long long v = *reinterpret_cast<const volatile unsigned long long*>(odd_x);
+    if (T < 512) v &= (1ull << (T / 8)) - 1ull;
+    return __builtin_amdgcn_readfirstlane((uint32_t)v | (uint32_t)(v >> 32)) != 0u;
+  };
   const int t = threadIdx.x;
   const int n0 = A.n[0], n1 = n0 + A.n[1], n2 = n1 + A.n[2], n3 = n2 + A.n[3],
             n4 = HI ? n3 : n3 + A.n[4];
@@ -231,6 +239,34 @@ __global__ __launch_bounds__(T, RV ? 4 : 2) void k_sweep(SweepArgs A) {
   if (form && !kOverlap &&
       !phase_start<T>(A.k, A.part_in, 2 * A.nblk, A.S, red, c1, c2, c3))
     return;
+  // the end of the sweep on the row that urow and off (at) stand for
+  auto finish = [&](uint32_t urow, uint32_t off, double2 x, double2 a) {
+    if (OP != kCheb) {
+      st<NTL>(at(A.y, urow, off), a);
+      return;
+    }
+    double wr = A.ct.scale * (a.x - A.ct.sigma * x.x);
+    double wi = A.ct.scale * (a.y - A.ct.sigma * x.y);
+    double2 pp = make_double2(0.0, 0.0);
+    if (!A.ct.first) pp = ld<NTL>(at(A.ct.prev, urow, off));
+    wr -= pp.x;
+    wi -= pp.y;
+    st<false>(at(A.ct.prev, urow, off), make_double2(wr, wi));
+    if (A.ct.acc) {
+      // t_{k-2} = prev, t_{k-1} = x and t_k = w are all here: psi is read and
+      // written at every third term only (7.2 vectors of traffic a term
+      // instead of 8.5; one step on 2^22 rows 8.9 -> 8.0 ms)
+      double2 q = ld<NTL>(at(A.ct.psi, urow, off));
+      q.x += A.ct.cp.x * pp.x - A.ct.cp.y * pp.y;
+      q.y += A.ct.cp.x * pp.y + A.ct.cp.y * pp.x;
+      q.x += A.ct.cx.x * x.x - A.ct.cx.y * x.y;
+      q.y += A.ct.cx.x * x.y + A.ct.cx.y * x.x;
+      q.x += A.ct.ck.x * wr - A.ct.ck.y * wi;
+      q.y += A.ct.ck.x * wi + A.ct.ck.y * wr;
+      st<NTL>(at(A.ct.psi, urow, off), q);
+    }
+  };
+  bool redo = false;  // a tile holds an infinity or a NaN
   for (int tile = Q.first; tile < Q.end; tile += Q.stride) {
     const uint32_t tr = (uint32_t)tile << (HI ? A.low : TB);
     const uint32_t row0 = tr | rt;
@@ -294,7 +330,9 @@ __global__ __launch_bounds__(T, RV ? 4 : 2) void k_sweep(SweepArgs A) {
           w = e.term == k ? A.tw.w[k] : w;
           w2 = e.term2 == k ? A.tw.w[k] : w2;
         }
-        we[t] = {e.off, e.pmask, e.rpar, 0u,
+        const uint32_t has0 = OP != kLanczos && (e.v0 != 0.0 || e.w0 != 0.0 || e.b0 != 0.0 || e.d0 != 0.0);
+        const uint32_t has1 = OP != kLanczos && (e.v1 != 0.0 || e.w1 != 0.0 || e.b1 != 0.0 || e.d1 != 0.0);
+        we[t] = {e.off, e.pmask, e.rpar, has0 | has1 << 1,
                  fma(w2, e.b0, w * e.v0), fma(w2, e.b1, w * e.v1),
                  fma(w2, e.d0, w * e.w0), fma(w2, e.d1, w * e.w1)};
       }
@@ -303,6 +341,15 @@ __global__ __launch_bounds__(T, RV ? 4 : 2) void k_sweep(SweepArgs A) {
     }
 #pragma unroll
     for (int r = 0; r < R; ++r) xt[t + r * T] = xo[r];
+    if (OP != kLanczos) {
+      // wavefronts that hold an infinity or a NaN (in the recurrence one makes
+      // every norm, and so the whole state, not finite)
+      double z = 0.0;
+#pragma unroll
+      for (int r = 0; r < R; ++r) z = fma(xo[r].x, 0.0, fma(xo[r].y, 0.0, z));
+      const bool odd = __ballot(z != 0.0) != 0ull;
+      if ((t & 63) == 0) odd_x[t >> 6] = odd;
+    }
     __syncthreads();
     if (!HI) {
       for (int i = n3; i < n4; ++i) {
@@ -414,6 +461,10 @@ __global__ __launch_bounds__(T, RV ? 4 : 2) void k_sweep(SweepArgs A) {
       }
 #undef CFET_FLIP
     }
+    if (OP != kLanczos && __builtin_expect(any_odd(), 0)) {
+      redo = true;
+      continue;
+    }
     if (OP == kLanczos) {
 #pragma unroll
       for (int r = 0; r < R; ++r) {
@@ -422,33 +473,49 @@ __global__ __launch_bounds__(T, RV ? 4 : 2) void k_sweep(SweepArgs A) {
       }
       if (last) continue;
     }
-    if (OP == kCheb) {
 #pragma unroll
+    for (int r = 0; r < R; ++r) finish(tr | rr[r], tb, xo[r], acc[r]);
+  }
+  if (OP != kLanczos && __builtin_expect(redo, 0)) {
+    // The loops above multiply by the zeros of entries that the operator does
+    // not store, which an infinity or a NaN in the tile must not meet: such
+    // tiles again, a row at a time, over the stored entries only.  (Looking for
+    // them costs a Chebyshev run 0.5 to 2 %: 2^22 rows 3120 -> 3154 us, 2^19 622 ->
+    // 629.)
+    for (int tile = Q.first; tile < Q.end; tile += Q.stride) {
+      const uint32_t tr = (uint32_t)tile << (HI ? A.low : TB);
+      __syncthreads();
+      double z = 0.0;
+#pragma unroll 1
       for (int r = 0; r < R; ++r) {
-        double wr = A.ct.scale * (acc[r].x - A.ct.sigma * xo[r].x);
-        double wi = A.ct.scale * (acc[r].y - A.ct.sigma * xo[r].y);
-        double2 pp = make_double2(0.0, 0.0);
-        if (!A.ct.first) pp = ld<NTL>(at(A.ct.prev, tr | rr[r], tb));
-        wr -= pp.x;
-        wi -= pp.y;
-        st<false>(at(A.ct.prev, tr | rr[r], tb), make_double2(wr, wi));
-        if (A.ct.acc) {
-          // t_{k-2} = prev, t_{k-1} = x and t_k = w are all here: psi is read and
-          // written at every third term only (7.2 vectors of traffic a term
-          // instead of 8.5; one step on 2^22 rows 8.9 -> 8.0 ms)
-          double2 q = ld<NTL>(at(A.ct.psi, tr | rr[r], tb));
-          q.x += A.ct.cp.x * pp.x - A.ct.cp.y * pp.y;
-          q.y += A.ct.cp.x * pp.y + A.ct.cp.y * pp.x;
-          q.x += A.ct.cx.x * xo[r].x - A.ct.cx.y * xo[r].y;
-          q.y += A.ct.cx.x * xo[r].y + A.ct.cx.y * xo[r].x;
-          q.x += A.ct.ck.x * wr - A.ct.ck.y * wi;
-          q.y += A.ct.ck.x * wi + A.ct.ck.y * wr;
-          st<NTL>(at(A.ct.psi, tr | rr[r], tb), q);
-        }
+        const double2 x = A.x[tr | row_of((uint32_t)(t + r * T))];
+        z = fma(x.x, 0.0, fma(x.y, 0.0, z));
+        xt[t + r * T] = x;
       }
-    } else {
-#pragma unroll
-      for (int r = 0; r < R; ++r) st<NTL>(at(A.y, tr | rr[r], tb), acc[r]);
+      const bool mine = __ballot(z != 0.0) != 0ull;
+      if ((t & 63) == 0) odd_x[t >> 6] = mine;
+      __syncthreads();
+      if (!any_odd()) continue;
+#pragma unroll 1
+      for (int r = 0; r < R; ++r) {
+        const uint32_t q = (uint32_t)(t + r * T);
+        const uint32_t row = tr | row_of(q);
+        double2 a = make_double2(0.0, 0.0);
+        if (!HI) {
+          a = A.y[row];
+          const double d = A.diag ? A.diag[row] : 0.0;
+          if (d != 0.0) acc_fma<true>(a, dv2{A.wdiag * d, 0.0}, xt[q]);
+        }
+#pragma unroll 1
+        for (int i = 0; i < n4; ++i) {
+          const WElem& e = we[i];
+          const uint32_t p = (uint32_t)__popc(row & e.pmask) & 1u;
+          if (!((e.has >> p) & 1u)) continue;
+          const double2 x = HI || i < n3 ? xt[q ^ e.off] : A.x[row ^ e.off];
+          acc_fma<RV>(a, value_of<RV>(e, p), x);
+        }
+        finish(row, 0u, xt[q], a);
+      }
     }
   }
   if (OP == kLanczos) {
@@ -500,7 +567,7 @@ constexpr int threads_of(int tb) { return tb >= 10 ? 512 : 256; }
 
 size_t lds_of(int tb) {
   return (size_t(16) << tb) + kSweepTerms * sizeof(WElem) +
-         2 * (threads_of(tb) / 64) * sizeof(double);
+         2 * (threads_of(tb) / 64) * sizeof(double) + 8;
 }
 
 template <int TB, bool RV, bool HI, int OP, bool NTL>

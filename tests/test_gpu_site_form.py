@@ -310,3 +310,55 @@ def test_few_entries_where_no_csr_is_kept():
     ref = np.zeros(n, complex)
     ref[at] = 1.7 * d * x[at]
     assert rel(y, ref) < 1e-14
+
+
+@pytest.mark.parametrize("L", [17, 19, 21])
+@pytest.mark.parametrize("complex_values,diag", [(False, False), (True, True)])
+def test_nonfinite_elements_reach_the_rows_that_couple_to_them(L, complex_values, diag):
+    # an infinity or a NaN meets no entry that the operator does not store
+    rng = np.random.default_rng(7 * L + complex_values)
+    n = 1 << L
+    offs = flips(L, rng, far=True)
+    H0 = strings(L, offs if L < 20 else offs[::2], rng, complex_values, sparse=True, diag=diag)
+    H1 = strings(L, offs[:9], rng, complex_values, sparse=True, diag=False)
+    x = I.random_state(n, rng)
+    bad = [5, n // 3, n - 7]
+    x[bad[0]] = complex(np.inf, 0.0)
+    x[bad[1]] = complex(0.1, np.nan)
+    x[bad[2]] = complex(-np.inf, np.nan)
+    with B.Propagator(H0, [H1], COS[:1]) as P:
+        y = P.apply(dev(x), 0.9, [-0.4]).cpu().numpy()
+        assert P.stats()["matrix_bytes"] < 16 * n        # on the sweeps
+    hit = np.zeros(n)
+    for H in (H0, H1):
+        M = H.to_scipy()
+        hit += abs(M[:, bad]) @ np.ones(len(bad))
+    assert np.array_equal(np.isfinite(y), hit == 0.0)
+    ok = hit == 0.0
+    assert 0 < np.count_nonzero(~ok) < 150
+    clean = np.where(np.isfinite(x), x, 0.0)
+    ref = 0.9 * (H0.to_scipy() @ clean) - 0.4 * (H1.to_scipy() @ clean)
+    assert rel(y[ok], ref[ok]) < 1e-14
+
+
+def test_nonfinite_sector_chebyshev():
+    # bonds and pair flips keep the parity of a row's bits: a NaN stays in its half
+    L = 17
+    rng = np.random.default_rng(17)
+    n = 1 << L
+    H0 = I.heisenberg_chain(L, 1.0, rng.uniform(-1, 1, L))
+    H1 = strings(L, [5 << b for b in range(L - 2)], rng, False, sparse=True, diag=False)
+    x = I.random_state(n, rng)
+    odd = parity(np.arange(n)) == 1
+    out = []
+    for poison in (False, True):
+        z = x.copy()
+        if poison:
+            z[1] = complex(np.nan, 0.0)
+        with B.Propagator(H0, [H1], COS[:1]) as P:
+            psi = dev(z)
+            P.propagate_chebyshev(psi, 0.0, 0.02, 1, "CF4:2", 1e-10)
+            assert P.stats()["matrix_bytes"] < 16 * n
+            out.append(psi.cpu().numpy())
+    assert np.all(np.isfinite(out[0])) and not np.all(np.isfinite(out[1][odd]))
+    assert rel(out[1][~odd], out[0][~odd]) < 1e-13
