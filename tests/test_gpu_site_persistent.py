@@ -262,3 +262,19 @@ def test_a_team_spread_over_the_xcds_gives_the_same_bits(model, L):
                 assert P.stats()["status"] == 0
     for a, b in zip(*got):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("model,L", [("heisenberg", 8), ("spins", 9), ("ising", 10), ("ising", 12),
+                                     ("heisenberg", 13)])
+@pytest.mark.parametrize("power", [-513, 505])
+def test_very_small_and_large_norms(model, L, power):
+    # ||psi||^2 = 2^-1026: its reciprocal overflows, its root's does not.  Squares of
+    # the elements round to multiples of 2^-1074, a part 2^(L - 49) of the sum at
+    # most; a dozen vectors leave 1e-9 of that.
+    H0, Hk, drives, psi0 = chain(model, L, L)
+    with B.Propagator(H0, Hk, drives) as P:
+        a, b = dev(psi0), dev(psi0 * 2.0 ** power)
+        P.propagate(a, 0.0, 0.04, 2, "CF4:2", 12)
+        P.propagate(b, 0.0, 0.04, 2, "CF4:2", 12)
+        assert P.stats()["status"] == 0
+    assert rel(b.cpu().numpy() * 2.0 ** -power, a.cpu().numpy()) < 1e-9
