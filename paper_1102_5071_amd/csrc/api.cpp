@@ -1887,7 +1887,7 @@ int cfet_create(const cfet_csr* H0, int32_t nterms, const cfet_csr* Hk, const cf
   }
   if (e == hipSuccess && c->parity.ok) {
     c->parity.nblk = cfet::parity_grid(c->parity.plan, c->num_cus);
-    e = hipMalloc(&c->parity.part, size_t(4) * size_t(c->parity.nblk) * sizeof(double2));
+    e = hipMalloc(&c->parity.part, cfet::parity_part_bytes(c->parity.nblk));
     cfet::PElem el[2 * cfet::kSweepTerms] = {};
     cfet::parity_tables(c->parity.plan, el, c->parity.n);
     if (e == hipSuccess) e = hipMalloc(&c->parity.e, sizeof(el));
@@ -2278,6 +2278,7 @@ int cfet_propagate_static(cfet_ctx* c, void* psi_dev, double t0, double dt, int6
   auto up = [](size_t b) { return (b + 255) & ~size_t(255); };
   const size_t np = size_t(std::max(2 * c->plan.nb_spmv, c->plan.nb_vec));
   const size_t nn = size_t(c->n);
+  static_assert(sizeof(LzScalars) <= 3072, "what fits the scratch depends on it");
   const size_t off_a = up(sizeof(LzScalars));
   const size_t off_b = off_a + up(np * sizeof(double));
   const size_t off_pv = off_b + up(np * sizeof(double));

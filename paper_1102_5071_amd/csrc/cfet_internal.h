@@ -48,7 +48,6 @@ struct LzScalars {
   int32_t brk[kMaxM];        // brk[j] = 1: the recursion stopped at or before step j
   int32_t m_eff;             // effective Krylov dimension (final after the small exponential)
   int32_t pad;
-  double scale[kMaxM];       // scale[k] = max over t < k of |alpha_t| + beta_t (sweep kernels)
 };
 
 // Device-side statistics and latched status.

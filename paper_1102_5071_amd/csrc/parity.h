@@ -111,6 +111,7 @@ struct SweepArgs {
   double2* y;               // result: the first sweep writes its part, the second adds to it
   const double* diag;
   LzScalars* S;
+  double* scale;            // scale[k]: max over t < k of |alpha_t| + beta_t
   const double2* part_in;   // the last phase's records: first sweep [0, nblk), second [nblk, 2 nblk)
   double2* part_out;
   double wdiag;
@@ -127,12 +128,14 @@ struct DevParity {
   double* diag = nullptr;   // device
   PElem* e = nullptr;       // device: first sweep's terms, second sweep's
   int n[2][5] = {};         // their group sizes
-  double2* part = nullptr;  // device: 2 sets x 2 sweeps x nblk records
+  double2* part = nullptr;  // device: 2 sets x 2 sweeps x nblk records, then kMaxM
+                            // doubles (SweepArgs::scale)
   int nblk = 0;
   int64_t bytes = 0;        // operator bytes one application reads
 };
 
 int parity_grid(const ParityPlan& P, int num_cus);
+size_t parity_part_bytes(int nblk);
 hipError_t parity_prepare();
 // The terms of the two sweeps in the kernels' order and groups (host; sweep 0,
 // 1 at e + sweep * kSweepTerms).

@@ -82,14 +82,14 @@ __device__ __forceinline__ void thread_records(const double2* __restrict__ p, in
 // k - 1, its alpha and norm, the early-stop rule.  False when the recurrence
 // has stopped; else the coefficients of u_k.  Block 0 writes the scalars.
 template <int T>
-__device__ bool phase_start(int k, const double2* part, int np, LzScalars* S, double* red,
-                            double& c1, double& c2, double& c3) {
+__device__ bool phase_start(int k, const double2* part, int np, LzScalars* S, double* scale,
+                            double* red, double& c1, double& c2, double& c3) {
   const bool first = blockIdx.x == 0 && threadIdx.x == 0;
   if (S->brk[k - 1]) {
     if (first && k < kMaxM) S->brk[k] = 1;
     return false;
   }
-  const double sc_prev = (k >= 2) ? S->scale[k - 2] : 0.0;
+  const double sc_prev = (k >= 2) ? scale[k - 2] : 0.0;
   const double al_prev = (k >= 2) ? S->alpha[k - 2] : 0.0;
   const double inv_prev = (k >= 2) ? S->inv_nrm[k - 2] : 0.0;
   double s1, s2;
@@ -109,7 +109,7 @@ __device__ bool phase_start(int k, const double2* part, int np, LzScalars* S, do
   if (first) {
     if (k == 1) S->beta0 = nu;
     else S->beta[k - 2] = nu;
-    S->scale[k - 1] = sc;
+    scale[k - 1] = sc;
     if (k < kMaxM) S->brk[k] = stop ? 1 : 0;
     if (stop) {
       S->m_eff = k - 1;
@@ -237,7 +237,7 @@ __global__ __launch_bounds__(T, RV ? 4 : 2) void k_sweep(SweepArgs A) {
   // has several tiles
   constexpr bool kOverlap = R <= 4;
   if (form && !kOverlap &&
-      !phase_start<T>(A.k, A.part_in, 2 * A.nblk, A.S, red, c1, c2, c3))
+      !phase_start<T>(A.k, A.part_in, 2 * A.nblk, A.S, A.scale, red, c1, c2, c3))
     return;
   // the end of the sweep on the row that urow and off (at) stand for
   auto finish = [&](uint32_t urow, uint32_t off, double2 x, double2 a) {
@@ -285,7 +285,7 @@ __global__ __launch_bounds__(T, RV ? 4 : 2) void k_sweep(SweepArgs A) {
         if (A.k >= 2) b[r] = ld<NTL>(at(A.u2, tr | rr[r], tb));
       }
       if (kOverlap && fresh &&
-          !phase_start<T>(A.k, A.part_in, 2 * A.nblk, A.S, red, c1, c2, c3))
+          !phase_start<T>(A.k, A.part_in, 2 * A.nblk, A.S, A.scale, red, c1, c2, c3))
         return;
 #pragma unroll
       for (int r = 0; r < R; ++r) {
@@ -527,12 +527,13 @@ __global__ __launch_bounds__(T, RV ? 4 : 2) void k_sweep(SweepArgs A) {
 // End of the recurrence: the last alpha and norm, then the small exponential
 // and the recombination coefficients.
 __global__ __launch_bounds__(64) void k_parity_small(const double2* part, int np, LzScalars* S,
-                                                     int m, double dt, DevStats* stats) {
+                                                     double* scale, int m, double dt,
+                                                     DevStats* stats) {
   __shared__ double lds[kChebMaxTerms];
   __shared__ double red[4];
   const int lane = threadIdx.x;
   double c1, c2, c3;
-  const bool done = !phase_start<64>(m, part, np, S, red, c1, c2, c3);
+  const bool done = !phase_start<64>(m, part, np, S, scale, red, c1, c2, c3);
   __threadfence_block();
   __syncthreads();
   const volatile LzScalars* V = S;  // written by lane 0 above
@@ -652,6 +653,10 @@ int parity_grid(const ParityPlan& P, int num_cus) {
   return std::min(1 << (P.nb - std::max(P.tbh, P.tbl)), 2 * std::max(num_cus, 1));
 }
 
+size_t parity_part_bytes(int nblk) {
+  return size_t(4) * size_t(nblk) * sizeof(double2) + kMaxM * sizeof(double);
+}
+
 // Allows the kernels on the largest tile their LDS (above 64 KiB).
 hipError_t parity_prepare() {
   const hipError_t e = allow_values<true>();
@@ -720,6 +725,7 @@ hipError_t launch_parity_lanczos(const DevParity& P, const TermWeights& tw, doub
                                  EventPool* events, hipStream_t st) {
   SweepArgs H = sweep_args(P, tw, 0), L = sweep_args(P, tw, 1);
   H.S = L.S = S;
+  H.scale = L.scale = reinterpret_cast<double*>(P.part + size_t(4) * size_t(P.nblk));
   H.m = L.m = m;
   const size_t set = size_t(2) * size_t(P.nblk);
   for (int k = 0; k < m; ++k) {
@@ -745,7 +751,7 @@ hipError_t launch_parity_lanczos(const DevParity& P, const TermWeights& tw, doub
     }
   }
   hipLaunchKernelGGL(k_parity_small, dim3(1), dim3(64), 0, st,
-                     P.part + size_t((m - 1) & 1) * set, 2 * P.nblk, S, m, dt, stats);
+                     P.part + size_t((m - 1) & 1) * set, 2 * P.nblk, S, H.scale, m, dt, stats);
   return hipGetLastError();
 }
 

@@ -88,3 +88,26 @@ def test_static_scratch_rejects_oversize():
         # m = 2 fits (one basis vector of 16 MiB)
         P.propagate_static(psi, 0.0, 0.01, 1, "CF4:2", 2)
         assert P.stats()["status"] == 0
+
+
+def test_static_scratch_limit():
+    # 64 MiB hold the Lanczos scalars (3 KiB), two arrays of 4096 partial sums and
+    # one basis vector of 4190016 rows, exactly
+    n = ((64 << 20) - 3072 - 2 * 4096 * 8) // 16
+    assert n == 4190016
+    for rows, fits in ((n, True), (n + 1, False)):
+        d = np.linspace(-1.0, 1.0, rows)
+        drives = [{"kind": "cos", "A": 0.7, "omega": 1.3, "phi": 0.2}]
+        with B.Propagator(I.diagonal(d), [I.diagonal(d[::-1].copy())], drives, path="multi",
+                          reorder=False) as P:
+            psi0 = torch.full((rows,), rows ** -0.5, dtype=torch.complex128, device="cuda")
+            psi, ref = psi0.clone(), psi0.clone()
+            if fits:
+                P.propagate_static(psi, 0.0, 1e-3, 1, "CF4:2", 2)
+                P.propagate(ref, 0.0, 1e-3, 1, "CF4:2", 2)
+                assert P.stats()["status"] == 0
+                assert torch.equal(psi, ref) and not torch.equal(psi, psi0)
+            else:
+                with pytest.raises(B.CfetError) as e:
+                    P.propagate_static(psi, 0.0, 1e-3, 1, "CF4:2", 2)
+                assert e.value.code == 1 and torch.equal(psi, psi0)
