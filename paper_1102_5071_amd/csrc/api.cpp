@@ -2453,25 +2453,40 @@ int cfet_gradient(cfet_ctx* c, const void* psi0_dev, const void* target_dev, dou
   // of them in the Frechet kernels.  The call allocates its store, so it is kept
   // to 2 GiB; the 256 MiB of lambda bases hold 50 exponentials there.)
   const int rpath = choose_path_csr(c);
+  // The batches, too, are kept to what is free: shorter ones, and none if a single
+  // step's would not fit, so that a call needs no more than one exponential at a
+  // time does where little is left.
   const bool sited = rpath != 1 && c->site.ok && c->nterms == 1;
   const size_t step_bytes = size_t(sc.s) * size_t(m) * nn * sizeof(double2);
-  if (sited && N > 0 && N <= 16384 / sc.s && size_t(N) <= kGradWholeMax / step_bytes) {
-    size_t free_b = 0, total_b = 0;
-    if (hipMemGetInfo(&free_b, &total_b) == hipSuccess && size_t(N) * step_bytes <= free_b / 4)
-      seg = N;
-  }
+  size_t free_b = 0, total_b = 0;
+  if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) free_b = 0;
+  // partials of a launch of up to q steps (the last of a segment may hold fewer)
+  auto part_blocks = [&](int64_t q) {
+    size_t blocks = 0;
+    for (; q > 0; --q)
+      blocks = std::max(blocks, size_t(q) * sc.s * cfet::frechet_batch_blocks(n, int(q) * sc.s));
+    return blocks;
+  };
+  auto batch_bytes = [&](int64_t q) {
+    const size_t each = size_t(cfet::kMaxM) * cfet::kMaxM * sizeof(double2) + sizeof(LzScalars);
+    return size_t(q) * (step_bytes + size_t(sc.s) * each) +
+           part_blocks(q) * size_t(m) * size_t(m) * sizeof(double2);
+  };
+  // steps whose backward exponentials share a launch
+  int64_t bsteps = std::max<int64_t>(
+      1, std::min<int64_t>({N, int64_t(kGradBasisMax / step_bytes), 4096 / sc.s}));
+  while (sited && bsteps > 1 && batch_bytes(bsteps) > free_b / 8) bsteps /= 2;
+  const bool fits = sited && batch_bytes(bsteps) <= free_b / 8;
+  if (fits && N > 0 && N <= 16384 / sc.s && size_t(N) <= kGradWholeMax / step_bytes &&
+      size_t(N) * step_bytes <= free_b / 4)
+    seg = N;
   const int64_t nseg = (N + seg - 1) / seg;
   const size_t ystore = size_t(seg) * size_t(sc.s) * size_t(m) * nn * sizeof(double2);
-  bool keep = rpath != 1 && c->nterms == 1 && ystore <= kGradStoreMax;
-  if (keep) {
-    size_t free_b = 0, total_b = 0;
-    keep = hipMemGetInfo(&free_b, &total_b) == hipSuccess && ystore <= free_b / 2;
-  }
-  const bool batched = sited && keep;
+  const bool keep =
+      rpath != 1 && c->nterms == 1 && ystore <= kGradStoreMax && ystore <= free_b / 2;
+  const bool batched = fits && keep && ystore + batch_bytes(bsteps) <= free_b / 2;
   const bool whole = batched && nseg == 1;
-  // steps whose backward exponentials share a launch, and their exponentials
-  const int64_t bsteps = std::max<int64_t>(
-      1, std::min<int64_t>({seg, int64_t(kGradBasisMax / step_bytes), 4096 / sc.s}));
+  bsteps = std::min(bsteps, seg);
   const size_t bexp = size_t(bsteps) * size_t(sc.s);
   double2 *Yall = nullptr, *gval = nullptr;
   LzScalars* Tall = nullptr;
@@ -2484,10 +2499,7 @@ int cfet_gradient(cfet_ctx* c, const void* psi0_dev, const void* target_dev, dou
   if (e == hipSuccess && keep) e = gb.get(&Yall, size_t(seg) * size_t(sc.s) * size_t(m) * nn);
   if (e == hipSuccess && keep) e = gb.get(&Tall, size_t(seg) * size_t(sc.s));
   if (e == hipSuccess && batched) {
-    size_t blocks = 0;  // the last launch of a segment may hold fewer steps
-    for (int64_t q = 1; q <= bsteps; ++q)
-      blocks = std::max(blocks, size_t(q) * sc.s * cfet::frechet_batch_blocks(n, int(q) * sc.s));
-    e = gb.get(&cpart, blocks * size_t(m) * size_t(m));
+    e = gb.get(&cpart, part_blocks(bsteps) * size_t(m) * size_t(m));
     if (e == hipSuccess) e = gb.get(&gval, bexp);
   } else if (e == hipSuccess) {
     e = gb.get(&cpart, size_t(cfet::frechet_part_blocks(n)) * cfet::kMaxM * cfet::kMaxM);

@@ -278,3 +278,27 @@ def test_very_small_and_large_norms(model, L, power):
         P.propagate(b, 0.0, 0.04, 2, "CF4:2", 12)
         assert P.stats()["status"] == 0
     assert rel(b.cpu().numpy() * 2.0 ** -power, a.cpu().numpy()) < 1e-9
+
+
+def test_gradient_in_little_free_memory():
+    # 4100 small exponentials: their batches would take over 400 MiB; with less left
+    # on the device they come in shorter ones
+    L, N, dt = 2, 820, 0.01
+    H0, Hk, _, psi0 = chain("ising", L, 1)
+    rng = np.random.default_rng(2)
+    drives = [{"kind": "pwc", "t_edges": np.linspace(0.0, N * dt, 5), "u": rng.uniform(-1, 1, 4)}]
+    psi, target = dev(psi0), dev(I.random_state(1 << L, rng))
+    with B.Propagator(H0, Hk, drives) as P:
+        F, g = P.gradient(psi, target, 0.0, dt, N, "CF6:5Opt", 4)
+        torch.cuda.empty_cache()
+        hold = []
+        for _ in range(3):
+            spare = torch.cuda.mem_get_info()[0] - (200 << 20)
+            if spare > 0:
+                hold.append(torch.empty(spare, dtype=torch.uint8, device="cuda"))
+        assert torch.cuda.mem_get_info()[0] <= 210 << 20
+        Fs, gs = P.gradient(psi, target, 0.0, dt, N, "CF6:5Opt", 4)
+        assert P.stats()["status"] == 0
+        del hold
+        torch.cuda.empty_cache()
+    assert abs(Fs - F) <= 1e-12 and np.max(np.abs(gs - g)) <= 1e-10 * np.max(np.abs(g))
