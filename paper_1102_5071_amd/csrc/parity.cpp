@@ -38,7 +38,10 @@ struct Table {
   std::vector<Cand> c;
   int16_t slot[kSize];
   bool full = false;
-  Table() { std::fill(slot, slot + kSize, int16_t(-1)); }
+  Table() {
+    std::fill(slot, slot + kSize, int16_t(-1));
+    c.reserve(kParityMaxTerms + 1);  // threads fill it, which may not throw
+  }
   static uint32_t hash(uint32_t off, int term) {
     return ((off * 0x9E3779B1u) ^ (uint32_t(term) * 0x85EBCA6Bu)) >> 22;
   }
@@ -75,6 +78,8 @@ struct Table {
   }
 };
 
+// body(t, first, last) for nth parts of [0, count); body does not throw.  A part
+// whose thread cannot be started runs here.
 template <class Body>
 void on_threads(int64_t count, unsigned nth, Body body) {
   if (nth <= 1) {
@@ -82,8 +87,15 @@ void on_threads(int64_t count, unsigned nth, Body body) {
     return;
   }
   std::vector<std::thread> pool;
-  for (unsigned t = 0; t < nth; ++t)
-    pool.emplace_back([&, t]() { body(t, count * t / nth, count * (t + 1) / nth); });
+  pool.reserve(nth);
+  for (unsigned t = 0; t < nth; ++t) {
+    auto part = [&, t]() { body(t, count * t / nth, count * (t + 1) / nth); };
+    try {
+      pool.emplace_back(part);
+    } catch (...) {
+      part();
+    }
+  }
   for (auto& th : pool) th.join();
 }
 
@@ -290,7 +302,7 @@ std::vector<ParityTerm> merge_terms(const std::vector<ParityTerm>& terms) {
   return out;
 }
 
-bool plan_parity(const ParityForm& F, ParityPlan* P) {
+bool plan_parity(const ParityForm& F, ParityPlan* P) try {
   const int nb = F.nb;
   if (nb < kParityMinBits) return false;
   int tbh, tbl, low;
@@ -314,6 +326,8 @@ bool plan_parity(const ParityForm& F, ParityPlan* P) {
   // gathered terms cost a read of the vector from beyond the tile each: more
   // than a quarter of the terms and the other layouts serve better
   return 4 * P->far.size() <= terms.size() + 3;
+} catch (const std::bad_alloc&) {
+  return false;
 }
 
 }  // namespace cfet

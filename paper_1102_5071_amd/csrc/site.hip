@@ -32,6 +32,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <new>
 #include <type_traits>
 
 #include "parity.h"
@@ -876,7 +877,7 @@ size_t site_lds(const SitePlan& P) {
 
 }  // namespace
 
-bool plan_site(const ParityForm& F, SitePlan* P) {
+bool plan_site(const ParityForm& F, SitePlan* P) try {
   const int nb = F.nb;
   if (nb < 1) return false;
   SitePlan S;
@@ -961,6 +962,8 @@ bool plan_site(const ParityForm& F, SitePlan* P) {
   }
   *P = S;
   return true;
+} catch (const std::bad_alloc&) {
+  return false;
 }
 
 hipError_t site_prepare(const SitePlan& P, bool real, int num_cus, bool* fits) {
