@@ -40,7 +40,8 @@ DEFAULT_STEPS = {"hydrogen": (200, 20), "ising": (1000, 100), "heisenberg": (20,
                  "batched": (200, 20), "adjoint": (200, 20)}
 # the roofline each plain workload's dominant kernel is measured against: the
 # Heisenberg chain's two sweeps per Lanczos iteration stream their vectors from
-# HBM (8.5 vectors of 268 MB; 13 GB for the product alone in complex-CSR terms);
+# HBM (8.5 vectors of 268 MB, and 0.9 of gathers beyond the tiles; 13 GB for the
+# product alone in complex-CSR terms);
 # the hydrogen and Ising operators and Krylov bases stay in the caches and
 # their persistent kernels wait on grid-wide round trips
 BOUND = {"heisenberg": "hbm", "hydrogen": "latency", "ising": "latency"}
@@ -74,12 +75,6 @@ def exponential_algorithmic_bytes(dim, nnz_total, ncsr, m):
     (read m basis vectors, write psi: (m+1)*16 B per row)."""
     return (m * spmv_algorithmic_bytes(dim, nnz_total, ncsr) + (m - 1) * 64 * dim
             + (m + 1) * 16 * dim)
-
-
-def site_form(matrix_bytes, dim):
-    """True when the multi-kernel path runs on the site-term form: it stores at
-    most one double per row and its terms, every other layout more."""
-    return matrix_bytes <= 8 * dim + 65536
 
 
 def measured_traffic(kernel, key, chunk):
@@ -616,7 +611,7 @@ def run_plain(args):
     extra = {}
     if path == "multi":
         kernel = B.SPMV_KERNEL_NAMES[stp["layout"]]
-        if site_form(stp["matrix_bytes"], p.dim):
+        if P.form() == "site_sweeps":
             # one iteration: z_{k-1}, u_{k-1}, u_{k-2} read, u_k, z_k written
             # (Chebyshev term: x, t_{k-2} read, t_k written, psi at every third)
             kernel = "k_sweep"
@@ -637,7 +632,7 @@ def run_plain(args):
             # the Chebyshev path times its applies (no Lanczos epilogue)
             key += "_cheb"
             kernel = {"k_lz_spmv": "k_apply", "k_sell_lz_spmv": "k_sell_apply"}.get(kernel, kernel)
-    elif args.workload == "ising" and p.dim <= 1 << 14 and not args.path and not args.layout:
+    elif P.form() == "site_persistent":
         # site terms: per exponential the basis and the state
         # (u_k written and read back, psi written); the operator is in registers
         kernel = "k_site_one" if p.dim <= 1 << 10 else "k_site_team"

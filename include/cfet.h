@@ -127,8 +127,12 @@ typedef struct {
  * that depends on the parity of a few row bits, a real diagonal in one of the
  * terms -- runs from that compact form on kernels of its own: persistent up to
  * 2^14 rows (paths 2 and 3), two sweeps per Lanczos iteration from 2^16 rows
- * (path 1; also cfet_apply and cfet_propagate_chebyshev there).  Detection runs
- * on the host at cfet_create; same results up to the order of summation. */
+ * (path 1; also cfet_propagate_static, cfet_propagate_chebyshev and, from 9 * 2^18
+ * entries, cfet_apply).  Operators of few entries from 2^16 rows keep the other
+ * paths: fewer than 2^20 in all, or rows that the cooperative kernel holds in
+ * registers.  Above 2^22 rows, where one path is all there is, a path flag makes
+ * no difference.  Detection runs on the host at cfet_create; same results up to
+ * the order of summation. */
 /* Store the operator in sliced-ELL form (64-row slices, column-major, driven
  * terms first in each row) for the multi-kernel path.  Large dimensions
  * (n > 2^22, where only the multi-kernel path runs) default to
@@ -198,15 +202,15 @@ typedef struct {
                                 recombinations (microseconds, cumulative) */
   int32_t layout;            /* operator storage of the multi-kernel path: 0 merged CSR,
                                 1 SELL-64, 2 SELL-64 with shared parts, 3 the same split
-                                into two passes (CFET_LAYOUT_SELL_SPLIT) */
+                                into two passes (CFET_LAYOUT_SELL_SPLIT).  Where
+                                cfet_operator_form gives site terms: what the dimension
+                                alone would select, 0 or 3; not what is stored */
   int32_t reordered;         /* 1: the CSR paths run on their own row order (see
                                 CFET_NO_REORDER) */
   int64_t matrix_bytes;      /* stored operator bytes one application of that layout
                                 reads (values, columns, masks, row and slice data;
                                 padding excluded).  Where the multi-kernel path runs
-                                on the site-term form: that form's bytes, at most 8
-                                per row and its terms; layout then tells what the
-                                dimension alone would select */
+                                on site terms: at most 8 per row and the terms */
 } cfet_stats_t;
 
 /* Build a context for H(t) = H0 + sum_k f_k(t) Hk[k], k < nterms
@@ -235,8 +239,10 @@ CFET_API int cfet_propagate(cfet_ctx *c, void *psi_dev, double t0, double dt, in
  * call: code being captured into a HIP graph, tight serving loops, harnesses
  * that forbid allocation.  Same arguments, same result as cfet_propagate on
  * the multi-kernel path (CFET_FORCE_MULTIKERNEL), which it always takes; it
- * calls no hipMalloc/hipFree and allocates no host memory.  Its Krylov basis,
- * partial sums, Lanczos scalars and (for reordered operators) the state in the
+ * calls no hipMalloc/hipFree and allocates no host memory (a sum of site terms
+ * from 2^16 rows runs on the sweeps here too; their partial sums are the
+ * context's).  Its Krylov basis, partial sums, Lanczos scalars and (for
+ * reordered operators) the state in the
  * stored row order live in a fixed 64 MiB device array of the library, one
  * per GPU, set up by the first cfet_create on that GPU and held until the
  * process ends: it needs
@@ -357,6 +363,12 @@ CFET_API int cfet_apply(cfet_ctx *c, const void *x_dev, void *y_dev, double a, c
  * latched device status (which this call clears). */
 CFET_API int cfet_stats(cfet_ctx *c, cfet_stats_t *s);
 
+/* What cfet_propagate runs the operator from (see the flags of cfet_create):
+ * 0 the merged operator (on the multi-kernel path in cfet_stats_t.layout), 1 site
+ * terms in the persistent kernels (up to 2^14 rows), 2 site terms in the sweeps
+ * of the multi-kernel path (from 2^16 rows). */
+CFET_API int cfet_operator_form(cfet_ctx *c, int32_t *form);
+
 /* Release all device and host memory of the context (synchronises). */
 CFET_API int cfet_destroy(cfet_ctx *c);
 
@@ -449,7 +461,9 @@ typedef struct {
   double tune_us[12];     /* create-time timing (us) of one product, its reduction and
                              the three-term update, [i * 4 + j] for 128, 256, 512
                              threads per block (i) and 2, 4, 8, 16 rows per lane and
-                             pass (j); 0 if not timed.  The layout kept is, among those
+                             pass (j); 0 if not timed.  (The product of a batch of
+                             driven spin chains from 2^20 rows in all does not depend
+                             on the layout: it adds the same to each.)  The layout kept is, among those
                              within 3 % of the fastest, the one with the most rows per
                              block, then the fewest threads per block */
 } cfet_batch_stats_t;

@@ -31,7 +31,9 @@ KEEP_CSR = 0x4000
 TEST_FLAGS = {None: 0, "spread_team": 0x10000, "no_team": 0x20000}
 PATH_NAMES = {0: "none", 1: "multi", 2: "single", 3: "coop"}
 LAYOUT_NAMES = {0: "csr", 1: "sell", 2: "sell_uniform", 3: "sell_split"}
-# the kernel(s) of one Lanczos SpMV on the multi-kernel path, per layout
+FORM_NAMES = {0: "merged", 1: "site_persistent", 2: "site_sweeps"}
+# the kernel(s) of one Lanczos SpMV on the multi-kernel path, per layout (where
+# Propagator.form() is "merged"; k_sweep on site terms)
 SPMV_KERNEL_NAMES = {0: "k_lz_spmv", 1: "k_sell_lz_spmv", 2: "k_sell_lz_spmv",
                      3: "k_tile_pass1+k_tile_pass2"}
 MAX_KRYLOV = 64
@@ -118,6 +120,7 @@ def load():
                                    c_int32, POINTER(_DtChoice), c_void_p]
     lib.cfet_apply.argtypes = [c_void_p, c_void_p, c_void_p, c_double, c_void_p, c_void_p]
     lib.cfet_stats.argtypes = [c_void_p, POINTER(_Stats)]
+    lib.cfet_operator_form.argtypes = [c_void_p, POINTER(c_int32)]
     lib.cfet_destroy.argtypes = [c_void_p]
     lib.cfet_scheme_info.argtypes = [c_int32, POINTER(c_int32), POINTER(c_int32), c_void_p,
                                      c_void_p]
@@ -136,7 +139,7 @@ def load():
     lib.cfet_batch_destroy.argtypes = [c_void_p]
     lib.cfet_batch_last_error.restype = ctypes.c_char_p
     lib.cfet_batch_last_error.argtypes = [c_void_p]
-    for name in ("cfet_create", "cfet_propagate", "cfet_propagate_static", "cfet_gradient", "cfet_apply", "cfet_stats",
+    for name in ("cfet_create", "cfet_propagate", "cfet_propagate_static", "cfet_gradient", "cfet_apply", "cfet_stats", "cfet_operator_form",
                  "cfet_destroy", "cfet_scheme_info", "cfet_step_weights", "cfet_tridiag_expm",
                  "cfet_profile", "cfet_batch_create", "cfet_batch_propagate", "cfet_batch_stats",
                  "cfet_batch_set_layout", "cfet_batch_instance_matvecs", "cfet_batch_destroy"):
@@ -299,6 +302,12 @@ class Propagator:
         out = {f[0]: getattr(st, f[0]) for f in _Stats._fields_}
         out["segment_us"] = list(out["segment_us"])
         return out
+
+    def form(self) -> str:
+        """What the propagation runs the operator from (FORM_NAMES)."""
+        form = c_int32()
+        _check(load().cfet_operator_form(self._ctx, ctypes.byref(form)), self._ctx)
+        return FORM_NAMES[form.value]
 
     def uses_sell(self) -> bool:
         """True when the multi-kernel path runs on a SELL-64 layout."""

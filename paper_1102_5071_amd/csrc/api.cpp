@@ -2887,9 +2887,11 @@ int cfet_stats(cfet_ctx* c, cfet_stats_t* s) {
   s->min_m_eff = d.exponentials ? d.min_m_eff : 0;
   s->breakdowns = d.breakdowns;
   s->path = c->last_path;
-  s->layout = (c->parity.ok && c->n > kAutoCoopMaxN) ? 3 : !c->use_sell ? 0 : (c->hi.nuni ? 3 : (c->sell.nuni ? 2 : 1));
+  if (c->parity.ok && c->n > kAutoCoopMaxN) s->layout = 3;  // (cfet_operator_form)
+  else s->layout = !c->use_sell ? 0 : (c->hi.nuni ? 3 : (c->sell.nuni ? 2 : 1));
   s->reordered = c->perm ? 1 : 0;
-  s->matrix_bytes = c->parity.ok ? c->parity.bytes : c->use_sell ? c->sell_bytes : 20 * c->A.nnz + 8 * (c->n + 1);
+  s->matrix_bytes = c->parity.ok ? c->parity.bytes
+                    : c->use_sell ? c->sell_bytes : 20 * c->A.nnz + 8 * (c->n + 1);
   s->status = d.status;
   s->last_norm = std::sqrt(d.last_norm2);
   harvest_events(c);
@@ -2909,6 +2911,12 @@ int cfet_stats(cfet_ctx* c, cfet_stats_t* s) {
     c->stats_host->status = CFET_OK;
     if (e != hipSuccess) return hip_fail(c, e, "clear status");
   }
+  return CFET_OK;
+}
+
+int cfet_operator_form(cfet_ctx* c, int32_t* form) {
+  if (!c || !form) return fail(c, CFET_EINVAL, "null argument");
+  *form = c->site.ok ? 1 : c->parity.ok ? 2 : 0;
   return CFET_OK;
 }
 

@@ -362,3 +362,35 @@ def test_nonfinite_sector_chebyshev():
             out.append(psi.cpu().numpy())
     assert np.all(np.isfinite(out[0])) and not np.all(np.isfinite(out[1][odd]))
     assert rel(out[1][~odd], out[0][~odd]) < 1e-13
+
+
+@pytest.mark.parametrize("L,form", [(12, "site_persistent"), (15, "merged"), (17, "site_sweeps")])
+def test_the_form_is_told(L, form):
+    p = I.config_heisenberg(L=L)
+    with B.Propagator(p.H0, p.Hk, p.drives) as P:
+        assert P.form() == form
+    with B.Propagator(p.H0, p.Hk, p.drives, path="multi") as P:
+        assert P.form() == "merged"
+
+
+def test_split_layout_at_2_to_the_24_rows():
+    # the layout of large operators off the form, by its flag: sampled rows, and
+    # the state returns over a step forward and one back
+    p = I.config_heisenberg(L=24)
+    n, rng = p.dim, np.random.default_rng(24)
+    with B.Propagator(p.H0, p.Hk, p.drives, layout="sell_split") as P:
+        assert P.form() == "merged" and P.stats()["layout"] == 3
+        x = I.random_state(n, rng)
+        y = P.apply(dev(x), 0.83, [-1.7]).cpu().numpy()
+        rows = np.unique(np.concatenate([[0, 1, 63, 64, n - 64, n - 1],
+                                         rng.choice(n, 2000, replace=False)]))
+        ref = O.apply_rows(p.H0, p.Hk, 0.83, [-1.7], x, rows)
+        assert np.all(np.abs(y[rows] - ref) <= 1e-13 * (1.0 + np.abs(ref)))
+        del x, y
+        psi = dev(p.psi0)
+        P.propagate(psi, 0.0, p.dt, 1, p.scheme, p.m)
+        assert abs(torch.linalg.vector_norm(psi).item() - 1.0) < 1e-12
+        P.propagate(psi, p.dt, -p.dt, 1, p.scheme, p.m)
+        st = P.stats()
+        assert st["status"] == 0 and st["matvecs"] == 10 * p.m
+        assert rel(psi.cpu().numpy(), p.psi0) < 1e-10
