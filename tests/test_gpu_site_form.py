@@ -3,8 +3,10 @@ depend on one parity of the row's bits: sums of Pauli strings) against the
 general sparse product and the CPU oracle.
 
 The sizes take every tile of the sweeps (2^9 rows at 2^16, 2^10 at 2^17 and
-2^18, 2^11 at 2^19, 2^12 at 2^21) with and without terms that a tile cannot
-hold.  Bars as elsewhere: apply 1e-14, propagation 1e-10, Chebyshev its
+2^18, 2^11 at 2^19 to 2^22, 2^12 in the second sweep of 2^21 and from 2^23), for
+products with and without terms that a tile cannot hold; the recurrence and the
+Chebyshev series are compared with the oracle up to 2^18 rows and with the
+multi-kernel CSR path at 2^20 to 2^22, where the rows per thread differ.  Bars as elsewhere: apply 1e-14, propagation 1e-10, Chebyshev its
 tolerance; H applications equal the oracle's.
 """
 import numpy as np
@@ -394,3 +396,51 @@ def test_split_layout_at_2_to_the_24_rows():
         st = P.stats()
         assert st["status"] == 0 and st["matvecs"] == 10 * p.m
         assert rel(psi.cpu().numpy(), p.psi0) < 1e-10
+
+
+@pytest.mark.parametrize("model,L", [("spins", 19), ("heisenberg", 20), ("heisenberg", 21),
+                                     ("spins", 21), ("heisenberg", 22)])
+def test_four_and_eight_rows_per_thread_match_the_csr_path(model, L):
+    rng = np.random.default_rng(L)
+    if model == "spins":
+        H0, Hk, drives = I.noninteracting_spins(L, 0.3, 0.7, 1.1)
+    else:
+        H0, Hk, drives = I.heisenberg_chain(L, 1.0, rng.uniform(-1, 1, L)), [I.sigma_x_sum(L)], COS[:1]
+    psi0 = dev(I.random_product_state(L, rng))
+    got = []
+    for path in (None, "multi"):
+        with B.Propagator(H0, Hk, drives, path=path) as P:
+            assert (P.form() == "site_sweeps") == (path is None)
+            a, b = psi0.clone(), psi0.clone()
+            P.propagate(a, 0.1, 0.05, 1, "CF4:2", 18)
+            st = P.stats()
+            P.propagate_chebyshev(b, 0.1, 0.05, 1, "CF4:2", 1e-12)
+            assert P.stats()["status"] == 0
+            got.append((a, b, st["matvecs"]))
+    (a, b, mv), (ao, bo, mvo) = got
+    assert mv == mvo
+
+    def drel(x, y):
+        return (torch.linalg.vector_norm(x - y) / torch.linalg.vector_norm(y)).item()
+    assert drel(a, ao) <= 1e-10 and drel(b, bo) <= 1e-10
+
+
+def test_complex_values_on_the_largest_tiles():
+    # 2^23 rows: both sweeps on 2^12-row tiles, no CSR; sampled rows, and a step back
+    L, rng = 23, np.random.default_rng(23)
+    H0 = strings(L, [3, 3 << 11, 3 << 21], rng, False, sparse=True, diag=True)
+    H1 = strings(L, [1, 1 << 11, 1 << 12, 1 << 20, 1 << 22, 1 << 17], rng, True, sparse=False,
+                 diag=False)
+    x = I.random_state(1 << L, rng)
+    rows = np.unique(np.concatenate([[0, 1, (1 << L) - 1], rng.choice(1 << L, 3000)]))
+    with B.Propagator(H0, [H1], COS[:1]) as P:
+        assert P.form() == "site_sweeps" and not np.all(H1.val.imag == 0.0)
+        psi = dev(x)
+        y = P.apply(psi, 0.83, [-1.7]).cpu().numpy()
+        P.propagate(psi, 0.0, 0.05, 1, "CF4:2", 20)
+        P.propagate_chebyshev(psi, 0.05, -0.05, 1, "CF4:2", 1e-12)
+        assert P.stats()["status"] == 0
+        back = psi.cpu().numpy()
+    ref = O.apply_rows(H0, [H1], 0.83, [-1.7], x, rows)
+    assert np.all(np.abs(y[rows] - ref) <= 1e-13 * (1.0 + np.abs(ref)))
+    assert rel(back, x) < 1e-10

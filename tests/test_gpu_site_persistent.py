@@ -1,7 +1,7 @@
 """The persistent kernels on the site-operator form (one workgroup up to 2^10
 rows, a team of workgroups up to 2^14) against the CPU oracle, at every
-launch shape: fewer rows than a wavefront, one row per thread, several, teams
-of 8 to 32 blocks with one, two and four rows per thread.
+launch shape: fewer rows than a wavefront, one row per thread, two (2^10 rows),
+teams of 8 to 32 blocks with one row per thread.
 
 Bars: propagation 1e-10 and the oracle's number of H applications; gradient as
 in the gradient tests (1e-8 of its largest entry).
@@ -189,7 +189,7 @@ def test_few_driven_sites(L, sites):
 
 
 def test_two_streams_and_two_contexts():
-    # two contexts in flight on two streams, teams of 16 and 8 blocks
+    # two contexts in flight on two streams, teams of 32 and 16 blocks
     jobs = []
     for L in (13, 12):
         H0, Hk, drives, psi0 = chain("heisenberg", L, L)
