@@ -105,19 +105,24 @@ __global__ __launch_bounds__(kCBlock) void k_frechet_c(
 // rows in tiles of kDRows staged in LDS.
 constexpr int kDRows = 32;
 
-// blockIdx.y: exponential of a batch (vectors `stride` elements, partials
-// `pstride` apart).
+// BATCH (here and below): one exponential of several per blockIdx.y or blockIdx.x,
+// their vectors `stride` elements and partials `pstride` apart.  Single ones keep
+// kernels without the offsets: k_frechet_small_wave takes 19.4 us without, 22.0 with
+// them.
+template <bool BATCH>
 __global__ __launch_bounds__(kCBlock) void k_frechet_dots(
     int64_t n, const double2* __restrict__ lam0, const double2* __restrict__ lam_rest,
     const double2* __restrict__ Y, const LzScalars* __restrict__ Spsi,
     const LzScalars* __restrict__ Slam, double2* __restrict__ part, int64_t stride,
     int64_t pstride) {
-  lam0 += blockIdx.y * stride;
-  lam_rest += blockIdx.y * stride;
-  Y += blockIdx.y * stride;
-  Spsi += blockIdx.y;
-  Slam += blockIdx.y;
-  part += blockIdx.y * pstride;
+  if (BATCH) {
+    lam0 += blockIdx.y * stride;
+    lam_rest += blockIdx.y * stride;
+    Y += blockIdx.y * stride;
+    Spsi += blockIdx.y;
+    Slam += blockIdx.y;
+    part += blockIdx.y * pstride;
+  }
   __shared__ double2 Ys[kDRows][kMaxM];
   __shared__ double2 Us[kDRows][kMaxM];
   const int mp = Spsi->m_eff, ml = Slam->m_eff;
@@ -169,17 +174,19 @@ __global__ __launch_bounds__(kCBlock) void k_frechet_dots(
 
 // C[k][j] = inv_lam[k] inv_psi[j] * sum over blocks of the partials, one
 // wavefront per pair: lane l adds blocks l, l + 64, ... in order, then a fixed
-// butterfly over the lanes (the same order on every run).  blockIdx.y: exponential
-// of a batch.
+// butterfly over the lanes (the same order on every run).
+template <bool BATCH>
 __global__ __launch_bounds__(256) void k_frechet_c_reduce(const double2* __restrict__ part,
                                                           int nb, const LzScalars* Spsi,
                                                           const LzScalars* Slam,
                                                           double2* __restrict__ C,
                                                           int64_t pstride) {
-  part += blockIdx.y * pstride;
-  Spsi += blockIdx.y;
-  Slam += blockIdx.y;
-  C += (int64_t)blockIdx.y * kMaxM * kMaxM;
+  if (BATCH) {
+    part += blockIdx.y * pstride;
+    Spsi += blockIdx.y;
+    Slam += blockIdx.y;
+    C += (int64_t)blockIdx.y * kMaxM * kMaxM;
+  }
   const int mp = Spsi->m_eff, ml = Slam->m_eff;
   const int npairs = ml * mp;
   const int pair = blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6);
@@ -207,15 +214,18 @@ __global__ __launch_bounds__(256) void k_frechet_c_reduce(const double2* __restr
 // ml + mp, by v <- exp(M / q) v repeated q times (Taylor series of each factor
 // summed until the terms are below 1e-18 of the sum), then dz[p] += w * g for
 // the (piece, weight) pairs of this exponential.
+template <bool BATCH>
 __global__ __launch_bounds__(kSmallThreads) void k_frechet_small(
     const LzScalars* __restrict__ Spsi, const LzScalars* __restrict__ Slam,
     const double2* __restrict__ C, double dt, double2* __restrict__ dz, DevStats* stats,
     const GradRec* __restrict__ rec, int* cursor, double2* __restrict__ gout) {
   __shared__ double2 tb[2][2 * kMaxM];
   __shared__ double red[2];
-  Spsi += blockIdx.x;
-  Slam += blockIdx.x;
-  C += (int64_t)blockIdx.x * kMaxM * kMaxM;
+  if (BATCH) {
+    Spsi += blockIdx.x;
+    Slam += blockIdx.x;
+    C += (int64_t)blockIdx.x * kMaxM * kMaxM;
+  }
   const int ml = Slam->m_eff, mp = Spsi->m_eff;
   const int nm = ml + mp;
   const int r = threadIdx.x;
@@ -223,7 +233,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_frechet_small(
   // to the one before it (also for a zero state)
   if (cursor && r == 0) *cursor -= 1;
   if (ml == 0 || mp == 0) {  // a zero state: no contribution
-    if (gout && r == 0) gout[blockIdx.x] = make_double2(0.0, 0.0);
+    if (BATCH && r == 0) gout[blockIdx.x] = make_double2(0.0, 0.0);
     return;
   }
   // row r of C in registers when mp <= kSmallC (the Taylor loop then reads
@@ -326,7 +336,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_frechet_small(
     const double bb = Slam->beta0 * Spsi->beta0;
     const double2 g = make_double2(bb * vr.x, bb * vr.y);
     // (piece, weight) pairs of this exponential from its record
-    if (gout) {
+    if (BATCH) {
       gout[blockIdx.x] = g;
     } else {
       const int npairs = rec->np;
@@ -358,20 +368,23 @@ __device__ __forceinline__ double lane_above(double v) {  // lane r receives lan
   return __hiloint2double(hi, lo);
 }
 
+template <bool BATCH>
 __global__ __launch_bounds__(64) void k_frechet_small_wave(
     const LzScalars* __restrict__ Spsi, const LzScalars* __restrict__ Slam,
     const double2* __restrict__ C, double dt, double2* __restrict__ dz, DevStats* stats,
     const GradRec* __restrict__ rec, int* cursor, double2* __restrict__ gout) {
   __shared__ double2 tw[64];
-  Spsi += blockIdx.x;
-  Slam += blockIdx.x;
-  C += (int64_t)blockIdx.x * kMaxM * kMaxM;
+  if (BATCH) {
+    Spsi += blockIdx.x;
+    Slam += blockIdx.x;
+    C += (int64_t)blockIdx.x * kMaxM * kMaxM;
+  }
   const int ml = Slam->m_eff, mp = Spsi->m_eff;
   const int nm = ml + mp;
   const int r = threadIdx.x;
   if (cursor && r == 0) *cursor -= 1;
   if (ml == 0 || mp == 0) {  // a zero state: no contribution
-    if (gout && r == 0) gout[blockIdx.x] = make_double2(0.0, 0.0);
+    if (BATCH && r == 0) gout[blockIdx.x] = make_double2(0.0, 0.0);
     return;
   }
   double2 creg[kSmallC];
@@ -448,7 +461,7 @@ __global__ __launch_bounds__(64) void k_frechet_small_wave(
   if (r == 0) {
     const double bb = Slam->beta0 * Spsi->beta0;
     const double2 g = make_double2(bb * vr.x, bb * vr.y);
-    if (gout) {
+    if (BATCH) {
       gout[blockIdx.x] = g;
     } else {
       const int npairs = rec->np;
@@ -582,8 +595,8 @@ int frechet_part_blocks(int64_t n) {
 static hipError_t launch_c_reduce(const double2* part, int nb, const LzScalars* Spsi,
                                   const LzScalars* Slam, double2* C, hipStream_t st) {
   // one wavefront per pair in use (at most kMaxM^2; the kernel reads m_eff)
-  hipLaunchKernelGGL(k_frechet_c_reduce, dim3((kMaxM * kMaxM + 3) / 4), dim3(256), 0, st, part,
-                     nb, Spsi, Slam, C, int64_t(0));
+  hipLaunchKernelGGL(k_frechet_c_reduce<false>, dim3((kMaxM * kMaxM + 3) / 4), dim3(256), 0, st,
+                     part, nb, Spsi, Slam, C, int64_t(0));
   return hipGetLastError();
 }
 
@@ -591,8 +604,8 @@ hipError_t launch_frechet_dots(int64_t n, const double2* lam0, const double2* la
                                const double2* Y, const LzScalars* Spsi, const LzScalars* Slam,
                                double2* part, double2* C, hipStream_t st) {
   const int nb = frechet_dots_blocks(n);
-  hipLaunchKernelGGL(k_frechet_dots, dim3(nb), dim3(kCBlock), 0, st, n, lam0, lam_rest, Y, Spsi,
-                     Slam, part, int64_t(0), int64_t(0));
+  hipLaunchKernelGGL(k_frechet_dots<false>, dim3(nb), dim3(kCBlock), 0, st, n, lam0, lam_rest, Y,
+                     Spsi, Slam, part, int64_t(0), int64_t(0));
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   return launch_c_reduce(part, nb, Spsi, Slam, C, st);
@@ -626,19 +639,19 @@ hipError_t launch_frechet_batch(int64_t n, int m, int E, const double2* lam, con
                                 double2* dz, int K, DevStats* stats, hipStream_t st) {
   const int nb = frechet_batch_blocks(n, E);
   const int64_t pstride = int64_t(nb) * m * m;
-  hipLaunchKernelGGL(k_frechet_dots, dim3(nb, E), dim3(kCBlock), 0, st, n, lam, lam + n, Y, Spsi,
-                     Slam, part, int64_t(m) * n, pstride);
+  hipLaunchKernelGGL(k_frechet_dots<true>, dim3(nb, E), dim3(kCBlock), 0, st, n, lam, lam + n, Y,
+                     Spsi, Slam, part, int64_t(m) * n, pstride);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_frechet_c_reduce, dim3((m * m + 3) / 4, E), dim3(256), 0, st, part, nb,
+  hipLaunchKernelGGL(k_frechet_c_reduce<true>, dim3((m * m + 3) / 4, E), dim3(256), 0, st, part, nb,
                      Spsi, Slam, C, pstride);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (small_wave(m))
-    hipLaunchKernelGGL(k_frechet_small_wave, dim3(E), dim3(64), 0, st, Spsi, Slam, C, dt, dz,
+    hipLaunchKernelGGL(k_frechet_small_wave<true>, dim3(E), dim3(64), 0, st, Spsi, Slam, C, dt, dz,
                        stats, rec, static_cast<int*>(nullptr), g);
   else
-    hipLaunchKernelGGL(k_frechet_small, dim3(E), dim3(kSmallThreads), 0, st, Spsi, Slam, C, dt,
+    hipLaunchKernelGGL(k_frechet_small<true>, dim3(E), dim3(kSmallThreads), 0, st, Spsi, Slam, C, dt,
                        dz, stats, rec, static_cast<int*>(nullptr), g);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -652,10 +665,10 @@ hipError_t launch_frechet_small_rec(const LzScalars* Spsi, const LzScalars* Slam
                                     hipStream_t st) {
   if (!cur) return hipErrorInvalidValue;
   if (small_wave(mmax)) {
-    hipLaunchKernelGGL(k_frechet_small_wave, dim3(1), dim3(64), 0, st, Spsi, Slam, C, dt, dz,
+    hipLaunchKernelGGL(k_frechet_small_wave<false>, dim3(1), dim3(64), 0, st, Spsi, Slam, C, dt, dz,
                        stats, cur, cursor, static_cast<double2*>(nullptr));
   } else {
-    hipLaunchKernelGGL(k_frechet_small, dim3(1), dim3(kSmallThreads), 0, st, Spsi, Slam, C, dt,
+    hipLaunchKernelGGL(k_frechet_small<false>, dim3(1), dim3(kSmallThreads), 0, st, Spsi, Slam, C, dt,
                        dz, stats, cur, cursor, static_cast<double2*>(nullptr));
   }
   return hipGetLastError();
