@@ -446,6 +446,12 @@ CFET_API int cfet_batch_create(int32_t nops, const cfet_csr* ops, int32_t ninst,
     }
     flips = flips && real_diagonal(mats[inst[order[q].second].h0]);
   }
+  if (flips) {  // enough of them per row, over the batch's elements
+    double sum = 0.0;
+    for (int q = 0; q < ninst; ++q)
+      sum += double(mats[std::get<1>(order[q].first)[0]].nnz);
+    flips = sum >= double(cfet::kFlipMinPerRow) * double(b->user_total);
+  }
   // shared operators, one per key
   std::map<Key, std::tuple<int64_t*, uint32_t*, double2*>> shared;
   int slot = 0;

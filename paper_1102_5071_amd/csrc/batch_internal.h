@@ -32,8 +32,13 @@ constexpr int kFlipMaxBits = 21;    // packed elements of a group they serve
 // elements of a batch from which the flip sweeps are used: one tile per CU.
 // Below, they leave CUs idle and their extra launch shows (three steps of 64
 // chains of 2^12 and 2^13 rows, 0.4 M elements: 2.2 ms with k_b_spmm, 2.8 with
-// the sweeps; 64 of 2^11 to 2^15, 0.9 M: 3.2 and 3.1; four of 2^18: 3.4 and 2.8)
+// the sweeps; at 0.9 M, 64 of 2^11 to 2^15, 3.2 and 3.1; four of 2^18, 1.0 M, 3.4
+// and 2.8)
 constexpr int64_t kFlipMinElements = int64_t(1) << 20;
+// ... and flips per row, on average: k_b_spmm reads a neighbour for each, the sweeps
+// cost the same for all (two steps of 64 chains of 2^13 to 2^18 rows, one driven site
+// 3.84 ms with k_b_spmm, 4.48 with the sweeps; six 4.57 and 4.58; eight 4.73 and 4.55)
+constexpr int kFlipMinPerRow = 7;
 constexpr int kFlipGather = 3;      // bits above a tile that the low sweep gathers itself
 
 struct BGroup {

@@ -320,3 +320,34 @@ def test_flip_sweeps_match_oracle(sizes):
     assert list(mv) == list(rmv)
     for r, o in zip(refs, outs):
         assert rel(o, r) <= 1e-11
+
+
+@pytest.mark.parametrize("sites,groups", [(6, 1), (7, 2)])
+def test_few_flips_per_row_keep_the_gathering_product(sites, groups):
+    # 64 chains of 2^16 rows: one group, unless the flip sweeps take groups of 2^21
+    # elements; they do from seven flips a row
+    L, rng = 16, np.random.default_rng(sites)
+    X = I.sigma_x_sum(L)
+    at = np.arange(sites) * L // sites
+    ops = [I.CSR(X.n, np.arange(X.n + 1, dtype=np.int64) * sites,
+                 X.col.reshape(-1, L)[:, at].ravel(), X.val.reshape(-1, L)[:, at].ravel())]
+    insts = []
+    for j in range(64):
+        ops.append(I.ising_chain(L, 1.0, rng.uniform(-1, 1, L)))
+        insts.append({"h0": len(ops) - 1, "hk": [0],
+                      "drives": [{"kind": "cos", "A": float(rng.uniform(0.2, 1.5)),
+                                  "omega": float(rng.uniform(0.5, 3.0)), "phi": 0.3}],
+                      "psi0": I.random_state(1 << L, rng)})
+    with B.BatchPropagator(ops, insts) as P:
+        psi = torch.from_numpy(np.concatenate([i["psi0"] for i in insts])).to("cuda")
+        P.propagate(psi, 0.1, 0.03, 1, "CF4:2", 24, 1e-10)
+        st, mv = P.stats(), P.instance_matvecs()
+        outs = [v.cpu().numpy() for v in P.split(psi)]
+    assert st["status"] == 0 and st["ngroups"] == groups
+    pick = [0, 31, 32, 63]
+    resolved = [{"H0": ops[insts[j]["h0"]], "Hk": [ops[0]], "drives": insts[j]["drives"],
+                 "psi0": insts[j]["psi0"]} for j in pick]
+    stats = []
+    refs = O.propagate_batch(resolved, 0.1, 0.03, 1, "CF4:2", 24, 1e-10, stats=stats)
+    for j, r, s in zip(pick, refs, stats):
+        assert rel(outs[j], r) <= 1e-11 and mv[j] == s["n_matvec"]
