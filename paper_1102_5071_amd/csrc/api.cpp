@@ -1492,7 +1492,7 @@ int cfet_create(const cfet_csr* H0, int32_t nterms, const cfet_csr* Hk, const cf
       if (e == hipSuccess)
         e = hipMemcpy(*d, form.diag.data(), size_t(n) * sizeof(double), hipMemcpyHostToDevice);
     };
-    if (found && cfet::plan_site(form, &c->site.plan)) {
+    if (found && cfet::plan_site(form, c->max_row, &c->site.plan)) {
       int cus = 0;
       bool fits = false;
       e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device);

@@ -163,7 +163,8 @@ struct SitePlan {
   int nfar[2] = {0, 0};      // terms that leave the block, per set
   PElem e[kSiteSlots] = {};  // by slot
 };
-bool plan_site(const ParityForm& F, SitePlan* P);
+// max_row: stored entries of the longest row
+bool plan_site(const ParityForm& F, int max_row, SitePlan* P);
 
 struct DevSite {
   bool ok = false;

@@ -877,7 +877,7 @@ size_t site_lds(const SitePlan& P) {
 
 }  // namespace
 
-bool plan_site(const ParityForm& F, SitePlan* P) try {
+bool plan_site(const ParityForm& F, int max_row, SitePlan* P) try {
   const int nb = F.nb;
   if (nb < 1) return false;
   SitePlan S;
@@ -909,9 +909,14 @@ bool plan_site(const ParityForm& F, SitePlan* P) try {
   // driven terms need registers for twice the terms: at 2^14 rows they spill
   // and take 15 us (6.0).  Larger teams than 32 do not fit one XCD.  One
   // workgroup is kept up to 2^10 rows also where a team is faster (two sets: 3.4
-  // against 2.4), so that calls on several streams run side by side.
+  // against 2.4), so that calls on several streams run side by side.  There two sets
+  // spill (69 registers, 119 with complex values, as do 32 of the complex teams of
+  // 512), and short rows are left to the CSR kernel: rows of 11 entries 276 and 290 us
+  // (three steps), of 13 284 and 290, of 14 308 and 291, of 20 (a driven Heisenberg
+  // chain) 5.6 and 3.2 us an iteration.
   const bool simple = S.mode == kOneSet;
   S.R = 1;
+  if (nb == 10 && S.mode == kTwoSets && max_row <= 13) return false;
   if (nb <= 10) {
     S.blocks = 1;
     S.T = nb <= 6 ? 64 : nb <= 9 ? 1 << nb : 512;

@@ -302,3 +302,21 @@ def test_gradient_in_little_free_memory():
         del hold
         torch.cuda.empty_cache()
     assert abs(Fs - F) <= 1e-12 and np.max(np.abs(gs - g)) <= 1e-10 * np.max(np.abs(g))
+
+
+@pytest.mark.parametrize("sites,form", [(1, "merged"), (3, "merged"), (4, "site_persistent")])
+def test_short_rows_of_two_sets_at_2_to_the_10(sites, form):
+    # bonds and a few driven sites: rows of up to 13 entries stay on the CSR kernel
+    L, rng = 10, np.random.default_rng(sites)
+    X = I.sigma_x_sum(L)
+    Hk = I.CSR(X.n, np.arange(X.n + 1, dtype=np.int64) * sites,
+               X.col.reshape(-1, L)[:, :sites].ravel(), X.val.reshape(-1, L)[:, :sites].ravel())
+    H0, _, drives, psi0 = chain("heisenberg", L, L)
+    ref = O.propagate(H0, [Hk], drives, psi0, 0.0, 0.05, 2, "CF4:2", m=12)
+    with B.Propagator(H0, [Hk], drives) as P:
+        assert P.form() == form
+        psi = dev(psi0)
+        P.propagate(psi, 0.0, 0.05, 2, "CF4:2", 12)
+        st = P.stats()
+        assert st["status"] == 0 and B.PATH_NAMES[st["path"]] == "single"
+        assert rel(psi.cpu().numpy(), ref) <= 1e-10
