@@ -474,7 +474,7 @@ CFET_API int cfet_batch_create(int32_t nops, const cfet_csr* ops, int32_t ninst,
     const int64_t n = mats[inst[t0].h0].n;
     const int sh = std::get<2>(key);
     const std::vector<int>& hk = std::get<1>(key);
-    if (!shared.count(key)) {
+    if (!flips && !shared.count(key)) {  // (the flip sweeps read no stored operator)
       // merged rows: H0 (term 0, if shared), then H_1 .. H_K
       std::vector<const HostCSR*> terms;
       std::vector<int> tid;
@@ -532,10 +532,46 @@ CFET_API int cfet_batch_create(int32_t nops, const cfet_csr* ops, int32_t ninst,
     while (g.lpr < g.B) g.lpr <<= 1;
     g.slot0 = slot;
     g.shared_h0 = sh >= 0 ? 1 : 0;
-    g.rowptr = std::get<0>(shared[key]);
-    g.colt = std::get<1>(shared[key]);
-    g.val = std::get<2>(shared[key]);
-    if (sh < 0) {
+    if (!flips) {
+      g.rowptr = std::get<0>(shared[key]);
+      g.colt = std::get<1>(shared[key]);
+      g.val = std::get<2>(shared[key]);
+    }
+    if (flips) {
+      // factors by element bit, real H0 diagonal [n][B], tiles
+      const int B = g.B;
+      int lb = 0;
+      while ((1 << lb) < B) ++lb;
+      cfet::BFlip fl{};
+      fl.nv = lb;
+      while ((int64_t(1) << (fl.nv - lb)) < n) ++fl.nv;
+      std::vector<double> cf(24, 0.0), dr(size_t(n) * B, 0.0);
+      const std::vector<double>& f = flip_of[key];
+      for (size_t i = 0; i < f.size(); ++i) cf[i + size_t(lb)] = f[i];
+      for (int j = 0; j < B; ++j) {
+        const HostCSR& h = mats[inst[order[slot + j].second].h0];
+        for (int64_t r = 0; r < n; ++r)
+          if (h.rp[r] < h.rp[r + 1]) dr[size_t(r) * B + j] = h.val[2 * h.rp[r]];
+      }
+      double *dc = nullptr, *dv = nullptr;
+      e = dalloc(&dc, cf.size());
+      if (e == hipSuccess) b->allocs.push_back(dc);
+      if (e == hipSuccess) e = dalloc(&dv, dr.size());
+      if (e == hipSuccess) b->allocs.push_back(dv);
+      if (e == hipSuccess)
+        e = hipMemcpy(dc, cf.data(), cf.size() * sizeof(double), hipMemcpyHostToDevice);
+      if (e == hipSuccess)
+        e = hipMemcpy(dv, dr.data(), dr.size() * sizeof(double), hipMemcpyHostToDevice);
+      if (e != hipSuccess) {
+        rc = bhip(b, e, "cfet_batch_create: H0 upload");
+        break;
+      }
+      fl.coef = dc;
+      fl.diagr = dv;
+      fl.sblocks = 1 << std::max(0, fl.nv - cfet::kFlipBits);
+      fl.hblocks = fl.nv - cfet::kFlipBits > cfet::kFlipGather ? fl.sblocks : 0;
+      b->flips.push_back(fl);
+    } else if (sh < 0) {
       // per-instance H0: dense diagonal [n][B] and off-diagonal rows [B][n + 1]
       const int B = g.B;
       std::vector<double> diag(size_t(2) * n * B, 0.0);
@@ -562,39 +598,12 @@ CFET_API int cfet_batch_create(int32_t nops, const cfet_csr* ops, int32_t ninst,
         }
         rpj[n] = int64_t(ocol.size());
       }
-      if (!flips) {
-        double2* dd = nullptr;
-        e = dalloc(&dd, size_t(n) * B);
-        if (e == hipSuccess) b->allocs.push_back(dd);
-        if (e == hipSuccess)
-          e = hipMemcpy(dd, diag.data(), diag.size() * sizeof(double), hipMemcpyHostToDevice);
-        g.diag = dd;
-      } else {
-        // factors by element bit, real diagonal, tiles
-        int lb = 0;
-        while ((1 << lb) < B) ++lb;
-        cfet::BFlip fl{};
-        fl.nv = lb;
-        while ((int64_t(1) << (fl.nv - lb)) < n) ++fl.nv;
-        std::vector<double> cf(24, 0.0), dr(diag.size() / 2);
-        const std::vector<double>& f = flip_of[key];
-        for (size_t i = 0; i < f.size(); ++i) cf[i + size_t(lb)] = f[i];
-        for (size_t q = 0; q < dr.size(); ++q) dr[q] = diag[2 * q];
-        double *dc = nullptr, *dv = nullptr;
-        e = dalloc(&dc, cf.size());
-        if (e == hipSuccess) b->allocs.push_back(dc);
-        if (e == hipSuccess) e = dalloc(&dv, dr.size());
-        if (e == hipSuccess) b->allocs.push_back(dv);
-        if (e == hipSuccess)
-          e = hipMemcpy(dc, cf.data(), cf.size() * sizeof(double), hipMemcpyHostToDevice);
-        if (e == hipSuccess)
-          e = hipMemcpy(dv, dr.data(), dr.size() * sizeof(double), hipMemcpyHostToDevice);
-        fl.coef = dc;
-        fl.diagr = dv;
-        fl.sblocks = 1 << std::max(0, fl.nv - cfet::kFlipBits);
-        fl.hblocks = fl.nv - cfet::kFlipBits > cfet::kFlipGather ? fl.sblocks : 0;
-        b->flips.push_back(fl);
-      }
+      double2* dd = nullptr;
+      e = dalloc(&dd, size_t(n) * B);
+      if (e == hipSuccess) b->allocs.push_back(dd);
+      if (e == hipSuccess)
+        e = hipMemcpy(dd, diag.data(), diag.size() * sizeof(double), hipMemcpyHostToDevice);
+      g.diag = dd;
       if (e == hipSuccess && any_off) {
         int64_t* drp = nullptr;
         int32_t* dcol = nullptr;
