@@ -299,7 +299,8 @@ CFET_API int cfet_propagate_chebyshev(cfet_ctx *c, void *psi_dev, double t0, dou
  * psi0_dev, target_dev: complex128[n] device buffers (read only).  Writes
  * *F_out and dFdu_out[0..K-1] (host) and synchronises hip_stream.  Device
  * workspace O((sqrt(nsteps) s + 2 m) n) -- with kept projections up to 16 GiB,
- * at most half of the free memory --, allocated for the call.  Needs the
+ * batches of backward exponentials up to some 600 MiB, together at most half of
+ * the free memory --, allocated for the call.  Needs the
  * CSR operator: kept for n <= 2^22, above that only with CFET_KEEP_CSR at
  * create (CFET_EUNSUPPORTED otherwise). */
 CFET_API int cfet_gradient(cfet_ctx *c, const void *psi0_dev, const void *target_dev, double t0,

@@ -226,7 +226,7 @@ hipError_t enqueue_step(const BLaunch& L, int m, int s_count, hipStream_t s) {
 // with the fewest wavefronts per block: the other kernels of a step (the
 // second reduction, the recombination) pay per block and per partial, and a
 // smaller block waits at its barrier for fewer wavefronts, none of which this
-// timing shows.
+// timing shows.  (On the flip sweeps the product is the same for every layout.)
 int autotune(cfet_batch* b) {
   hipError_t e = hipSuccess;
   hipEvent_t e0 = nullptr, e1 = nullptr;

@@ -268,6 +268,10 @@ namespace {
 // the price of a few more gathered terms in the second; vectors that the
 // memory-side cache holds want the fewest gathered terms; small ones want a
 // tile for every CU (2^18 rows: 17.0 us with 2^10-row tiles, 23.1 with 2^11).
+// The two sizes between, by measurement (Ising chain, one step): 2^21 rows 5.23 ms
+// with the second sweep on 2^12-row tiles, 5.39 on 2^11; 2^22 rows, whose working
+// set is at the edge of that cache, 10.4 ms with 128-byte segments, 12.0 with
+// 64-byte ones and 12.4 with those and 2^12-row tiles in the second sweep.
 void tiles_of(int nb, int* tbh, int* tbl, int* low) {
   if (nb >= 23) {
     *tbh = *tbl = 12;

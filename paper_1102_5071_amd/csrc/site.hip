@@ -8,7 +8,9 @@
 // thread keeps, in registers and for the whole launch, the LDS address and the
 // value of each term on its rows and its rows' diagonal: no matrix is read, and
 // a term costs its read and its multiply-adds.  (Decoding a table of terms in
-// every iteration, from LDS or by v_readlane, cost 100 to 250 cycles a term.)
+// every iteration, from LDS or by v_readlane, cost 100 to 250 cycles a term.  Where
+// the terms are too many for the registers, plan_site says which shapes, they
+// spill.)
 // The recurrence is the pipelined one of persistent.hip,
 //     u_k = (z_{k-1} - alpha_{k-1} u_{k-1}) / nu_{k-1} - (nu_{k-1} / nu_{k-2}) u_{k-2},
 // z_k = H_w u_k, alpha_k = <u_k, z_k> / nu_k^2, nu_k = ||u_k||.
