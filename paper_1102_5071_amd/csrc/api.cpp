@@ -122,7 +122,7 @@ int64_t coop_grid_blocks(int64_t n, int cus) {
 }
 // True if the cooperative kernel runs an operator of this longest row with at
 // most kParityCoopTail of its entries outside registers.
-bool coop_serves(int64_t n, int nterms, int max_row, bool real, int device) {
+bool coop_serves(int64_t n, int nterms, int max_row, int device) {
   if (n > kAutoCoopMaxN) return false;
   int cus = 0, most = 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess ||
@@ -131,7 +131,7 @@ bool coop_serves(int64_t n, int nterms, int max_row, bool real, int device) {
   const int64_t blocks = coop_grid_blocks(n, cus);
   const int p = cfet::persistent_choose_preset(max_row, (n + blocks - 1) / blocks, false);
   return p >= 0 && max_row <= cfet::persistent_row_entries(p, false) + kParityCoopTail &&
-         cfet::persistent_max_blocks(p, nterms, real, &most) == hipSuccess && most >= blocks;
+         cfet::persistent_max_blocks(p, nterms, false, &most) == hipSuccess && most >= blocks;
 }
 
 // device bytes the gradient may spend on keeping the recomputed projections
@@ -248,10 +248,7 @@ void free_ctx(cfet_ctx* c) {
   if (c->sell.cval) (void)hipFree(c->sell.cval);
   if (c->hi.ccolt) (void)hipFree(c->hi.ccolt);
   if (c->hi.cval) (void)hipFree(c->hi.cval);
-  if (c->site.diag) (void)hipFree(c->site.diag);
-  if (c->site.e) (void)hipFree(c->site.e);
   if (c->site.rec) (void)hipFree(c->site.rec);
-  if (c->site.ids) (void)hipFree(c->site.ids);
   if (c->parity.diag) (void)hipFree(c->parity.diag);
   if (c->parity.e) (void)hipFree(c->parity.e);
   if (c->parity.part) (void)hipFree(c->parity.part);
@@ -1481,48 +1478,42 @@ int cfet_create(const cfet_csr* H0, int32_t nterms, const cfet_csr* Hk, const cf
   // (cfet_gradient runs on it).
   const uint32_t layout_flags = CFET_LAYOUT_SELL | CFET_LAYOUT_SELL_UNIFORM | CFET_LAYOUT_SELL_SPLIT;
   const uint32_t path_flags = CFET_FORCE_MULTIKERNEL | CFET_FORCE_SINGLE | CFET_FORCE_COOPERATIVE;
-  if (!(flags & layout_flags) && (n > kAutoCoopMaxN || !(flags & path_flags))) {
-    const unsigned nth =
-        n < 65536 ? 1u : std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
+  // Looked for only where a plan may take it: up to 2^13 rows, at 2^14 with one
+  // operator that may be a diagonal, and from kParityMinN.
+  const bool sites = n <= (int64_t(1) << 13) ||
+                     (n == (int64_t(1) << 14) && nterms == 1 && std::min(mats[0].nnz, mats[1].nnz) <= n);
+  const bool sweeps = n >= kParityMinN && nnz >= kParityMinNnz &&
+                      !coop_serves(n, nterms, c->max_row, c->device);
+  if ((sites || sweeps) && !(flags & layout_flags) &&
+      (n > kAutoCoopMaxN || !(flags & path_flags))) {
+    const unsigned most = std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
+    const unsigned nth = unsigned(std::min<int64_t>(most, std::max<int64_t>(1, nnz >> 16)));
     cfet::ParityForm form;
     const bool found = cfet::find_parity_form(mats, nterms, n, nth, &form);
-    auto upload_diag = [&](double** d) {
-      if (form.diag_term < 0 || e != hipSuccess) return;
-      e = hipMalloc(d, size_t(n) * sizeof(double));
-      if (e == hipSuccess)
-        e = hipMemcpy(*d, form.diag.data(), size_t(n) * sizeof(double), hipMemcpyHostToDevice);
-    };
-    if (found && cfet::plan_site(form, c->max_row, &c->site.plan)) {
+    if (found && sites && cfet::plan_site(form, c->max_row, &c->site.plan)) {
       int cus = 0;
       bool fits = false;
       e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device);
       if (e == hipSuccess) e = cfet::site_prepare(c->site.plan, form.real, cus, &fits);
       if (e == hipSuccess && fits) {
         c->site.ok = true;
-        c->site.real = form.real;
-        c->site.diag_term = form.diag_term;
-        upload_diag(&c->site.diag);
-        if (e == hipSuccess) e = hipMalloc(&c->site.e, sizeof(c->site.plan.e));
-        if (e == hipSuccess)
-          e = hipMemcpy(c->site.e, c->site.plan.e, sizeof(c->site.plan.e), hipMemcpyHostToDevice);
-        if (e == hipSuccess) e = hipMalloc(&c->site.rec, 3 * cfet::kSiteRecs * 16);
-        if (e == hipSuccess) e = hipMemset(c->site.rec, 0, 3 * cfet::kSiteRecs * 16);
-        if (e == hipSuccess) e = hipMalloc(&c->site.ids, 257 * sizeof(unsigned long long));
-        if (e == hipSuccess) e = hipMemset(c->site.ids, 0, 257 * sizeof(unsigned long long));
-        c->site.count = c->site.ids + 256;
+        e = cfet::site_upload(form, &c->site);
         c->site.skew = (flags & CFET_TEST_NO_TEAM) ? 1 : 0;
         c->site.spread = (flags & CFET_TEST_SPREAD_TEAM) ? 1 : 0;
       }
     }
-    if (found && n >= kParityMinN && nnz >= kParityMinNnz &&
-        !coop_serves(n, nterms, c->max_row, form.real, c->device) &&
-        cfet::plan_parity(form, &c->parity.plan)) {
+    if (found && sweeps && cfet::plan_parity(form, &c->parity.plan)) {
       c->parity.ok = true;
       c->parity.real = form.real;
       c->parity.diag_term = form.diag_term;
       c->parity.bytes = int64_t(form.terms.size()) * int64_t(sizeof(cfet::PElem)) +
                         (form.diag_term >= 0 ? 8 * n : 0);
-      upload_diag(&c->parity.diag);
+      if (form.diag_term >= 0) {
+        e = hipMalloc(&c->parity.diag, size_t(n) * sizeof(double));
+        if (e == hipSuccess)
+          e = hipMemcpy(c->parity.diag, form.diag.data(), size_t(n) * sizeof(double),
+                        hipMemcpyHostToDevice);
+      }
     }
   }
   const bool use_sell = !c->parity.ok && ((flags & layout_flags) || n > kAutoCoopMaxN);
@@ -1895,8 +1886,10 @@ int cfet_create(const cfet_csr* H0, int32_t nterms, const cfet_csr* Hk, const cf
     if (e == hipSuccess) e = cfet::parity_prepare();
   }
   if (c->hi.nuni) c->nb_tile = cfet::tile_grid(n, c->tbits, c->num_cus);
-  c->preset_single = need_csr ? cfet::persistent_choose_preset(c->max_row, n, true) : -1;
-  if (e == hipSuccess && c->num_cus > 0 && need_csr) {
+  // (the site kernels stand in for the persistent CSR ones wherever they serve)
+  c->preset_single =
+      need_csr && !c->site.ok ? cfet::persistent_choose_preset(c->max_row, n, true) : -1;
+  if (e == hipSuccess && c->num_cus > 0 && need_csr && !c->site.ok) {
     const int64_t nbw = coop_grid_blocks(n, c->num_cus);
     const int64_t rows = (n + nbw - 1) / nbw;
     c->preset_coop = cfet::persistent_choose_preset(c->max_row, rows, false);

@@ -12,35 +12,39 @@ namespace cfet {
 
 namespace {
 
-uint64_t bits_of(double v) {
-  uint64_t u;
-  std::memcpy(&u, &v, sizeof(u));
-  return u;
-}
-
 struct Value {
   uint64_t re = 0, im = 0;  // bit patterns; 0, 0 also where nothing is stored
   bool operator==(const Value& o) const { return re == o.re && im == o.im; }
+  void get(double* out) const { std::memcpy(out, this, sizeof(*this)); }
 };
+Value value_of(const double* v) {
+  Value x;
+  std::memcpy(&x, v, sizeof(x));
+  return x;
+}
 
-// Per (term, offset): the distinct values its rows hold and how many rows do.
+// One (operator term, offset): its two values, the mask that picks one, and how
+// many rows store an entry of it that is not 0.
 struct Cand {
-  uint32_t off;
+  uint32_t off, pmask;
   int term;
-  int nval;
-  Value val[2];
+  Value v[2];
   int64_t count;
+  uint8_t nonzero[2];  // v[p] is not 0
 };
 
-// Candidates in order of first appearance with an open-addressing index.
+// Candidates with an open-addressing index.
 struct Table {
   static constexpr uint32_t kSize = 1024;
+  static constexpr int kPlaces = 64;
   std::vector<Cand> c;
   int16_t slot[kSize];
-  bool full = false;
+  // the candidate of the last row's entry at this place of this term: the next
+  // row's is often the same
+  int16_t guess[kMaxTerms + 1][kPlaces] = {};
   Table() {
     std::fill(slot, slot + kSize, int16_t(-1));
-    c.reserve(kParityMaxTerms + 1);  // threads fill it, which may not throw
+    c.reserve(kParityMaxTerms + 1);
   }
   static uint32_t hash(uint32_t off, int term) {
     return ((off * 0x9E3779B1u) ^ (uint32_t(term) * 0x85EBCA6Bu)) >> 22;
@@ -48,33 +52,26 @@ struct Table {
   int find(uint32_t off, int term) const {
     for (uint32_t h = hash(off, term);; h = (h + 1) % kSize) {
       const int i = slot[h];
-      if (i < 0) return -1;
-      if (c[i].off == off && c[i].term == term) return i;
+      if (i < 0 || (c[i].off == off && c[i].term == term)) return i;
     }
   }
-  int get(uint32_t off, int term) {
-    for (uint32_t h = hash(off, term);; h = (h + 1) % kSize) {
-      const int i = slot[h];
-      if (i >= 0) {
-        if (c[i].off == off && c[i].term == term) return i;
-        continue;
-      }
-      if (c.size() > size_t(kParityMaxTerms)) {
-        full = true;
-        return -1;
-      }
-      slot[h] = int16_t(c.size());
-      c.push_back({off, term, 0, {}, 0});
-      return int(c.size()) - 1;
-    }
-  }
-  // false: a third distinct value
-  static bool add_value(Cand& k, const Value& v) {
-    for (int i = 0; i < k.nval; ++i)
-      if (k.val[i] == v) return true;
-    if (k.nval == 2) return false;
-    k.val[k.nval++] = v;
+  // false: there are too many
+  bool add(uint32_t off, int term) {
+    uint32_t h = hash(off, term);
+    for (; slot[h] >= 0; h = (h + 1) % kSize)
+      if (c[slot[h]].off == off && c[slot[h]].term == term) return true;
+    if (c.size() >= size_t(kParityMaxTerms)) return false;
+    slot[h] = int16_t(c.size());
+    c.push_back({off, 0u, term, {}, 0, {}});
     return true;
+  }
+  // find, of the entry at this place of a row (g: guess[term], p: c, not empty)
+  int at(int16_t* g, const Cand* p, uint32_t off, int term, int64_t place) const {
+    int i = g[place & (kPlaces - 1)];
+    if (p[i].off == off && p[i].term == term) return i;
+    i = find(off, term);
+    if (i >= 0) g[place & (kPlaces - 1)] = int16_t(i);
+    return i;
   }
 };
 
@@ -99,7 +96,7 @@ void on_threads(int64_t count, unsigned nth, Body body) {
   for (auto& th : pool) th.join();
 }
 
-inline uint32_t parity32(uint32_t v) { return uint32_t(__builtin_popcount(v)) & 1u; }
+inline uint32_t parity32(uint32_t v) { return uint32_t(__builtin_parity(v)); }
 
 }  // namespace
 
@@ -116,34 +113,87 @@ bool find_parity_form(const std::vector<HostCSR>& mats, int nterms, int64_t n, u
     for (int k = 0; k <= nterms; ++k) len += mats[k].rp[r + 1] - mats[k].rp[r];
     if (len > kParityMaxTerms + nterms + 1) return false;
   }
+  // A value that depends on one parity of the row's bits is told by row 0 and by
+  // the rows of a single bit: those give every term, its two values and its mask.
+  Table all;
+  for (int i = -1; i < nb; ++i) {
+    const int64_t r = i < 0 ? 0 : int64_t(1) << i;
+    for (int k = 0; k <= nterms; ++k)
+      for (int64_t q = mats[k].rp[r]; q < mats[k].rp[r + 1]; ++q) {
+        const uint32_t off = uint32_t(int64_t(mats[k].col[q]) ^ r);
+        if (off != 0 && !all.add(off, k)) return false;
+      }
+  }
+  auto value_at = [&](const Cand& k, int64_t r) {
+    const HostCSR& h = mats[k.term];
+    Value v;
+    for (int64_t q = h.rp[r]; q < h.rp[r + 1]; ++q)
+      if (uint32_t(int64_t(h.col[q]) ^ r) == k.off) v = value_of(h.val + 2 * q);
+    return v;
+  };
+  for (Cand& k : all.c) {
+    const Value a = value_at(k, 0);
+    Value b = a;
+    for (int i = 0; i < nb; ++i) {
+      const Value vi = value_at(k, int64_t(1) << i);
+      if (vi == a) continue;
+      if (!(b == a) && !(vi == b)) return false;  // a third value
+      b = vi;
+      k.pmask |= 1u << i;
+    }
+    if (k.pmask == 0 && a == Value{}) return false;  // stored zeros
+    k.v[0] = a;
+    k.v[1] = b;
+    for (int p = 0; p < 2; ++p) {
+      double v[2];
+      k.v[p].get(v);
+      k.nonzero[p] = v[0] != 0.0 || v[1] != 0.0;
+    }
+  }
+  // every stored value against the form, and every value the form says that is
+  // not stored (counted: the rows whose value is not 0 must be there)
   nth = std::max(1u, nth);
-  std::vector<Table> tab(nth);
+  std::vector<Table> tab(nth, all);
   std::atomic<bool> good{true};
   std::vector<int32_t> diag_terms(nth, 0);
+  F->diag.assign(size_t(n), 0.0);
   on_threads(n, nth, [&](unsigned t, int64_t r0, int64_t r1) {
     Table& T = tab[t];
+    Cand* const cand = T.c.data();
+    double* const diag = F->diag.data();
     int32_t dt = 0;
     for (int64_t r = r0; r < r1; ++r) {
       if ((r & 4095) == 0 && !good.load(std::memory_order_relaxed)) return;
       for (int k = 0; k <= nterms; ++k) {
-        const HostCSR& h = mats[k];
-        for (int64_t q = h.rp[r]; q < h.rp[r + 1]; ++q) {
-          const uint32_t off = uint32_t(int64_t(h.col[q]) ^ r);
-          const double re = h.val[2 * q], im = h.val[2 * q + 1];
+        const int64_t q0 = mats[k].rp[r], q1 = mats[k].rp[r + 1];
+        const int32_t* const col = mats[k].col;
+        const double* const val = mats[k].val;
+        for (int64_t q = q0; q < q1; ++q) {
+          const uint32_t off = uint32_t(int64_t(col[q]) ^ r);
           if (off == 0) {
             dt |= 1 << k;
-            if (im != 0.0) {
-              good.store(false);
-              return;
-            }
-            continue;
-          }
-          const int i = T.get(off, k);
-          if (i < 0 || !Table::add_value(T.c[i], Value{bits_of(re), bits_of(im)})) {
+            diag[r] = val[2 * q];
+            if (val[2 * q + 1] == 0.0) continue;
             good.store(false);
             return;
           }
-          T.c[i].count += 1;
+          const int i = T.c.empty() ? -1 : T.at(T.guess[k], cand, off, k, q - q0);
+          if (i >= 0) {
+            Cand& c = cand[i];
+            const uint32_t p = parity32(uint32_t(r) & c.pmask);
+            bool same = value_of(val + 2 * q) == c.v[p];
+            if (!same) {  // a zero of the other sign
+              double v[2];
+              c.v[p].get(v);
+              same = v[0] == val[2 * q] && v[1] == val[2 * q + 1];
+            }
+            if (same) {
+              c.count += c.nonzero[p];
+              continue;
+            }
+          }
+          good.store(false);
+          return;
         }
       }
     }
@@ -155,105 +205,21 @@ bool find_parity_form(const std::vector<HostCSR>& mats, int nterms, int64_t n, u
   if (dt & (dt - 1)) return false;
   for (int k = 0; k <= nterms; ++k)
     if (dt == (1 << k)) F->diag_term = k;
-  Table all;
-  for (const Table& T : tab)
-    for (const Cand& k : T.c) {
-      const int i = all.get(k.off, k.term);
-      if (i < 0) return false;
-      for (int v = 0; v < k.nval; ++v)
-        if (!Table::add_value(all.c[i], k.val[v])) return false;
-      all.c[i].count += k.count;
-    }
-  if (all.c.size() > size_t(kParityMaxTerms)) return false;
+  if (F->diag_term < 0) F->diag.clear();
+  for (size_t i = 0; i < all.c.size(); ++i) {
+    Cand& k = all.c[i];
+    for (const Table& T : tab) k.count += T.c[i].count;
+    if (k.count != (n / 2) * (k.nonzero[0] + k.nonzero[1])) return false;
+  }
   std::sort(all.c.begin(), all.c.end(), [](const Cand& a, const Cand& b) {
     return a.off != b.off ? a.off < b.off : a.term < b.term;
   });
-  auto value_at = [&](const Cand& k, int64_t r) {
-    const HostCSR& h = mats[k.term];
-    for (int64_t q = h.rp[r]; q < h.rp[r + 1]; ++q)
-      if (uint32_t(int64_t(h.col[q]) ^ r) == k.off)
-        return Value{bits_of(h.val[2 * q]), bits_of(h.val[2 * q + 1])};
-    return Value{};
-  };
-  auto put = [](const Value& v, double* out) {
-    std::memcpy(&out[0], &v.re, 8);
-    std::memcpy(&out[1], &v.im, 8);
-  };
-  bool two_valued = false;
   for (const Cand& k : all.c) {
-    ParityTerm p{k.off, 0u, k.term, {0.0, 0.0}, {0.0, 0.0}};
-    if (k.nval == 1 && k.count == n) {
-      put(k.val[0], p.v0);
-      put(k.val[0], p.v1);
-    } else {
-      // rows without an entry hold 0, the second value
-      const Value zero{};
-      Value a = k.val[0], b = k.nval == 2 ? k.val[1] : zero;
-      if (k.count != n && k.nval == 2) {
-        if (a == zero) a = b;  // stored zeros
-        else if (!(b == zero)) return false;
-        b = zero;
-      }
-      const Value at0 = value_at(k, 0);
-      if (!(at0 == a) && !(at0 == b)) return false;
-      for (int i = 0; i < nb; ++i) {
-        const Value vi = value_at(k, int64_t(1) << i);
-        if (!(vi == a) && !(vi == b)) return false;
-        if (!(vi == at0)) p.pmask |= 1u << i;
-      }
-      put(at0, p.v0);
-      put(at0 == a ? b : a, p.v1);
-      if (p.pmask == 0) return false;
-      two_valued = true;
-    }
+    ParityTerm p{k.off, k.pmask, k.term, {0.0, 0.0}, {0.0, 0.0}};
+    k.v[0].get(p.v0);
+    k.v[1].get(p.v1);
     if (p.v0[1] != 0.0 || p.v1[1] != 0.0) F->real = false;
     F->terms.push_back(p);
-  }
-  if (two_valued) {
-    // every stored value against the form, and every value the form says that
-    // is not stored (counted: the rows whose value is not 0 must be there)
-    std::vector<std::vector<int64_t>> seen(nth, std::vector<int64_t>(all.c.size(), 0));
-    Table idx;
-    for (size_t i = 0; i < all.c.size(); ++i) idx.get(all.c[i].off, all.c[i].term);
-    on_threads(n, nth, [&](unsigned t, int64_t r0, int64_t r1) {
-      for (int64_t r = r0; r < r1; ++r) {
-        if ((r & 4095) == 0 && !good.load(std::memory_order_relaxed)) return;
-        for (int k = 0; k <= nterms; ++k) {
-          const HostCSR& h = mats[k];
-          for (int64_t q = h.rp[r]; q < h.rp[r + 1]; ++q) {
-            const uint32_t off = uint32_t(int64_t(h.col[q]) ^ r);
-            if (off == 0) continue;
-            const int i = idx.find(off, k);
-            const ParityTerm& p = F->terms[i];
-            const double* v = parity32(uint32_t(r) & p.pmask) ? p.v1 : p.v0;
-            if (v[0] != h.val[2 * q] || v[1] != h.val[2 * q + 1]) {
-              good.store(false);
-              return;
-            }
-            if (v[0] != 0.0 || v[1] != 0.0) seen[t][i] += 1;
-          }
-        }
-      }
-    });
-    if (!good.load()) return false;
-    for (size_t i = 0; i < all.c.size(); ++i) {
-      const ParityTerm& p = F->terms[i];
-      const bool n0 = p.v0[0] != 0.0 || p.v0[1] != 0.0, n1 = p.v1[0] != 0.0 || p.v1[1] != 0.0;
-      int64_t want = 0, have = 0;
-      if (p.pmask == 0) want = n0 ? n : 0;
-      else want = (n0 ? n / 2 : 0) + (n1 ? n / 2 : 0);
-      for (unsigned t = 0; t < nth; ++t) have += seen[t][i];
-      if (want != have) return false;
-    }
-  }
-  if (F->diag_term >= 0) {
-    F->diag.assign(size_t(n), 0.0);
-    const HostCSR& h = mats[F->diag_term];
-    on_threads(n, nth, [&](unsigned, int64_t r0, int64_t r1) {
-      for (int64_t r = r0; r < r1; ++r)
-        for (int64_t q = h.rp[r]; q < h.rp[r + 1]; ++q)
-          if (int64_t(h.col[q]) == r) F->diag[size_t(r)] = h.val[2 * q];
-    });
   }
   return true;
 } catch (const std::bad_alloc&) {

@@ -171,10 +171,11 @@ struct DevSite {
   SitePlan plan;
   bool real = true;
   int diag_term = -1;
-  double* diag = nullptr;             // device (null: no diagonal)
-  PElem* e = nullptr;                 // device
-  void* rec = nullptr;                // device: 3 * kSiteRecs records
-  unsigned long long* ids = nullptr;  // device: XCD of each block of a launch, then the launch counter
+  void* rec = nullptr;                // device, the start of the allocation that holds all:
+                                      // 3 * kSiteRecs records
+  unsigned long long* ids = nullptr;  // XCD of each block of a launch, then the launch counter
+  PElem* e = nullptr;
+  double* diag = nullptr;             // (null: no diagonal)
   unsigned long long* count = nullptr;
   // tests: skew 1 makes a team wait for a launch that does not come (until the
   // wait's limit), spread 1 forms it from the first blocks of the grid
@@ -199,6 +200,8 @@ struct SiteArgs {
 
 // Sets up the plan's kernel; *fits: a launch's blocks are co-resident.
 hipError_t site_prepare(const SitePlan& P, bool real, int num_cus, bool* fits);
+// The device side of S->plan: one allocation (S->rec), one copy.
+hipError_t site_upload(const ParityForm& F, DevSite* S);
 // A whole call (see PersistArgs; basis, psi, wts and the exports are used).
 // host_wts: p.wts is a host table of nwts <= kSiteInlineW weights
 hipError_t launch_site(const DevSite& S, const PersistArgs& args, hipStream_t st, int nwts = 0);

@@ -34,6 +34,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstring>
 #include <new>
 #include <type_traits>
 
@@ -974,6 +975,10 @@ bool plan_site(const ParityForm& F, int max_row, SitePlan* P) try {
 }
 
 hipError_t site_prepare(const SitePlan& P, bool real, int num_cus, bool* fits) {
+  if (P.blocks == 1) {  // at most 512 threads and 64 KiB
+    *fits = true;
+    return hipSuccess;
+  }
   const void* fn = site_shape(P, real).fn;
   const size_t lds = site_lds(P);
   hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -981,8 +986,30 @@ hipError_t site_prepare(const SitePlan& P, bool real, int num_cus, bool* fits) {
   int per = 0;
   e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, fn, P.T, lds);
   if (e != hipSuccess) return e;
-  *fits = P.blocks == 1 ? per >= 1 : per * num_cus >= 8 * P.blocks;
+  *fits = per * num_cus >= 8 * P.blocks;
   return hipSuccess;
+}
+
+hipError_t site_upload(const ParityForm& F, DevSite* S) try {
+  const size_t ids = 3 * kSiteRecs * sizeof(Rec);
+  const size_t table = ids + 264 * sizeof(unsigned long long);  // 256 blocks, the counter
+  const size_t diag = table + sizeof(S->plan.e);
+  std::vector<unsigned char> h(diag + F.diag.size() * sizeof(double), 0);
+  std::memcpy(h.data() + table, S->plan.e, sizeof(S->plan.e));
+  if (!F.diag.empty())
+    std::memcpy(h.data() + diag, F.diag.data(), F.diag.size() * sizeof(double));
+  hipError_t e = hipMalloc(&S->rec, h.size());
+  if (e != hipSuccess) return e;
+  char* const d = static_cast<char*>(S->rec);
+  S->ids = reinterpret_cast<unsigned long long*>(d + ids);
+  S->count = S->ids + 256;
+  S->e = reinterpret_cast<PElem*>(d + table);
+  S->diag = F.diag.empty() ? nullptr : reinterpret_cast<double*>(d + diag);
+  S->real = F.real;
+  S->diag_term = F.diag_term;
+  return hipMemcpy(d, h.data(), h.size(), hipMemcpyHostToDevice);
+} catch (const std::bad_alloc&) {
+  return hipErrorOutOfMemory;
 }
 
 hipError_t launch_site(const DevSite& S, const PersistArgs& args, hipStream_t st, int nwts) {
