@@ -1,10 +1,17 @@
-// Recognition of the site-operator form when memory runs out: every allocation
-// in turn fails, on whichever thread makes it.  Prints the allocations of an
-// undisturbed run and how many of the disturbed ones still found the form.
+// Recognition of the site-operator form.  Without arguments: when memory runs
+// out, every allocation in turn fails, on whichever thread makes it; prints the
+// allocations of an undisturbed run and how many of the disturbed ones still
+// found the form.  With a seed: random sums of strings, rows in any column order,
+// as they are (the form has to be found) and changed in one place (it may not be);
+// prints how many of each were found.  A form found has to give the operator back.
 #include <atomic>
 #include <cstdio>
 #include <cstdlib>
+#include <algorithm>
+#include <complex>
+#include <map>
 #include <new>
+#include <random>
 #include <vector>
 
 #include "parity.h"
@@ -41,7 +48,99 @@ static cfet::HostCSR chain(int L, bool bonds) {
   return h;
 }
 
-int main() {
+typedef std::complex<double> cd;
+typedef std::vector<std::map<int, cd>> Rows;
+
+static int random_operators(unsigned seed) {
+  std::mt19937 g(seed);
+  auto below = [&](int n) { return int(g() % unsigned(n)); };
+  int whole = 0, trials = 0, changed = 0, tries = 0;
+  for (int trial = 0; trial < 300; ++trial) {
+    const int L = 2 + below(7), n = 1 << L, K = 1 + below(3);
+    std::vector<Rows> rows(size_t(K) + 1, Rows(size_t(n)));
+    const int diag = below(K + 2) - 1;
+    for (int k = 0; k <= K; ++k) {
+      for (int j = below(6); j >= 0; --j) {
+        const int off = 1 + below(n - 1), mask = below(3) ? below(n) : 0;
+        const cd a(below(4) ? 0.5 + below(9) : 0.0, below(3) ? 0.0 : 1.0 + below(5));
+        const cd b = mask ? (below(2) ? -a : below(2) ? cd(0.0, 0.0) : cd(1.25, 0.0)) : a;
+        if (a == cd(0.0, 0.0) && b == cd(0.0, 0.0)) continue;
+        if (rows[size_t(k)][0].count(off) || rows[size_t(k)][size_t(n - 1)].count((n - 1) ^ off))
+          continue;
+        bool free = true;
+        for (int r = 0; r < n; ++r) free = free && !rows[size_t(k)][size_t(r)].count(r ^ off);
+        for (int r = 0; free && r < n; ++r) {
+          const cd v = __builtin_parity(unsigned(r & mask)) ? b : a;
+          if (v != cd(0.0, 0.0)) rows[size_t(k)][size_t(r)][r ^ off] = v;
+        }
+      }
+      if (k == diag)
+        for (int r = 0; r < n; ++r)
+          if (below(5)) rows[size_t(k)][size_t(r)][r] = cd(double(below(7)), 0.0);
+    }
+    for (int pass = 0; pass < 2; ++pass) {
+      if (pass == 1) {  // one change
+        const int k = below(K + 1), r = below(n);
+        std::map<int, cd>& row = rows[size_t(k)][size_t(r)];
+        const int c = row.empty() || below(3) == 0 ? below(n) : std::next(row.begin(), below(int(row.size())))->first;
+        switch (below(5)) {
+          case 0: row.erase(c); break;
+          case 1: row[c] = cd(0.0, 0.0); break;
+          case 2: row[c] = cd(3.75, 0.0); break;
+          case 3: row[c] = cd(0.0, 2.5); break;
+          default: row[c] = cd(-0.0, -0.0); break;
+        }
+      }
+      std::vector<cfet::HostCSR> mats(size_t(K) + 1);
+      for (int k = 0; k <= K; ++k) {
+        cfet::HostCSR& h = mats[size_t(k)];
+        h.rp_buf.push_back(0);
+        for (int r = 0; r < n; ++r) {
+          std::vector<std::pair<int, cd>> e(rows[size_t(k)][size_t(r)].begin(),
+                                            rows[size_t(k)][size_t(r)].end());
+          std::shuffle(e.begin(), e.end(), g);
+          for (auto& x : e) {
+            h.col_buf.push_back(x.first);
+            h.val_buf.push_back(x.second.real());
+            h.val_buf.push_back(x.second.imag());
+          }
+          h.rp_buf.push_back(int64_t(h.col_buf.size()));
+        }
+        h.n = n;
+        h.nnz = int64_t(h.col_buf.size());
+        h.rp = h.rp_buf.data();
+        h.col = h.col_buf.data();
+        h.val = h.val_buf.data();
+      }
+      cfet::ParityForm F;
+      const bool found = cfet::find_parity_form(mats, K, n, 1u + unsigned(below(3)), &F);
+      (pass ? tries : trials) += 1;
+      (pass ? changed : whole) += found;
+      if (!found) continue;
+      bool real = true;
+      for (int k = 0; k <= K; ++k)
+        for (int r = 0; r < n; ++r) {
+          std::map<int, cd> form;
+          if (k == F.diag_term) form[r] = cd(F.diag[size_t(r)], 0.0);
+          for (const cfet::ParityTerm& t : F.terms)
+            if (t.term == k) {
+              const double* v = __builtin_parity(unsigned(r) & t.pmask) ? t.v1 : t.v0;
+              form[r ^ int(t.off)] += cd(v[0], v[1]);
+              real = real && v[1] == 0.0;
+            }
+          for (auto& x : rows[size_t(k)][size_t(r)]) form[x.first] -= x.second;
+          for (auto& x : form)
+            if (x.second != cd(0.0, 0.0)) return 1;
+        }
+      if (F.real != real) return 2;
+    }
+  }
+  std::printf("%d %d %d %d\n", trials, whole, tries, changed);
+  return 0;
+}
+
+int main(int argc, char** argv) {
+  if (argc > 1) return random_operators(unsigned(std::atoi(argv[1])));
   std::vector<cfet::HostCSR> mats;
   mats.push_back(chain(16, true));
   mats.push_back(chain(16, false));
