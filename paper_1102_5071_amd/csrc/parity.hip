@@ -193,7 +193,7 @@ constexpr int batch_of(int R) { return R <= 2 ? 4 : R == 4 ? 2 : 1; }
 
 // (Real values are held to 128 registers, two blocks a CU.  With eight rows per
 // thread, tiles of 2^12, that spills 20 in the first sweep of the recurrence and 18
-// in the second, 27 in the Chebyshev and 39 in the apply sweep.)
+// in the second, 26 in the Chebyshev and 38 in the apply sweep.)
 template <int TB, int T, bool RV, bool HI, int OP, bool NTL>
 __global__ __launch_bounds__(T, RV ? 4 : 2) void k_sweep(SweepArgs A) {
   constexpr int R = (1 << TB) / T;
@@ -203,9 +203,10 @@ __global__ __launch_bounds__(T, RV ? 4 : 2) void k_sweep(SweepArgs A) {
   WElem* we = reinterpret_cast<WElem*>(xt + (1 << TB));
   double* red = reinterpret_cast<double*>(we + kSweepTerms);
   // by wavefront: its part of the tile holds an infinity or a NaN
-  volatile uint8_t* odd_x = reinterpret_cast<uint8_t*>(red + 2 * (T / 64));
+  typedef __attribute__((address_space(3))) uint8_t* lds_bytes;
+  const lds_bytes odd_x = (lds_bytes)(uint8_t*)(red + 2 * (T / 64));
   auto any_odd = [&]() {
-    unsigned long long v = *reinterpret_cast<const volatile unsigned long long*>(odd_x);
+    unsigned long long v = *(__attribute__((address_space(3))) const unsigned long long*)odd_x;
     if (T < 512) v &= (1ull << (T / 8)) - 1ull;
     return __builtin_amdgcn_readfirstlane((uint32_t)v | (uint32_t)(v >> 32)) != 0u;
   };
@@ -486,8 +487,7 @@ __global__ __launch_bounds__(T, RV ? 4 : 2) void k_sweep(SweepArgs A) {
     // The loops above multiply by the zeros of entries that the operator does
     // not store, which an infinity or a NaN in the tile must not meet: such
     // tiles again, a row at a time, over the stored entries only.  (Looking for
-    // them costs a Chebyshev run 0.5 to 2 %: 2^22 rows 3120 -> 3154 us, 2^19 622 ->
-    // 629.)
+    // them costs a Chebyshev run up to 1 %: 2^22 rows 3144 -> 3157 us, 2^19 619 -> 626.)
     for (int tile = Q.first; tile < Q.end; tile += Q.stride) {
       const uint32_t tr = (uint32_t)tile << (HI ? A.low : TB);
       __syncthreads();
