@@ -436,7 +436,7 @@ __device__ __forceinline__ void site_run(const SiteArgs& A, int rank, double2* x
         gather(psi, g1);
       }
       for (int k = 0; k <= m; ++k) {
-        double c1 = 0.0, c2 = 0.0, c3 = 0.0, nu = 0.0, alpha = 0.0;
+        double c1 = 0.0, c2 = 0.0, c3 = 0.0, nu = 0.0;
         bool stop = false;
         // early-stop rule and records of phase k - 1 (off the path to u_k)
         auto record = [&]() {
@@ -451,7 +451,7 @@ __device__ __forceinline__ void site_run(const SiteArgs& A, int rank, double2* x
             sh.s1[k - 1] = S1;
             sh.s2[k - 1] = S2;
           }
-          alpha_prev = alpha;
+          alpha_prev = c2 * nu;
           inv_prev = c1;
         };
         if (k >= 1) {
@@ -476,8 +476,7 @@ __device__ __forceinline__ void site_run(const SiteArgs& A, int rank, double2* x
           // (c1 * c1 would overflow for norms below 7e-155)
           c1 = rsqrt(S2);
           nu = S2 > 0.0 ? S2 * c1 : S2;
-          alpha = S1 * c1 * c1;
-          c2 = alpha * c1;
+          c2 = S1 * c1 * c1 * c1;
           c3 = nu * inv_prev;
           if (k == m) {
             record();
